@@ -50,9 +50,11 @@
  * directly to the 16-bit inputs (n >= 128 only).  The environment variable
  * HADACORE_VARIANT set to "valu" or "mfma" forces one of them for n >= 128
  * (testing and tuning; read on every call); unset keeps the measured per-size
- * choice.
+ * choice.  For 2^16 < n < 2^20 "passes" and "parts" force one of the two ways of
+ * hadamard_transform_ws, and "parts-defer" also sets the waits of an in-place
+ * call to zero, so that its parts go through the workspace.
  *
- * Launches: a call is one kernel launch, or two for the two-pass sizes; m so
+ * Launches: a call is one kernel launch, or up to two for n > 2^16; m so
  * large that a launch would exceed 2^31 work-items (2^33 elements) is split
  * into several launches of consecutive rows on the same stream, with the
  * same result.
@@ -137,13 +139,20 @@ int64_t hadamard_transform_workspace_size(int64_t m, int64_t n);
 /*
  * hadamard_transform_ws -- as hadamard_transform_strided, for n up to 2^20.
  * Sizes above 2^16 (the paper's range ends at 2^15, Sec. 3.2) do not fit one
- * workgroup's registers in fp32, so they run in two passes
- * through a caller-provided fp32 workspace: pass 1 applies `scale` and the
- * stages on index bits 15..log2(n)-1 (between the 2^15-element blocks of a
- * row), pass 2 the stages on bits 0..14 within each block, and rounds once.
+ * workgroup's registers in fp32.  They run in one of two ways with the same
+ * results, chosen by measured speed from n, m and the mode.
+ *  - In one pass (most of 2^17 and 2^18, some of 2^19): several workgroups share
+ *    a row, each reading all of it and computing a part of the outputs.  In
+ *    place they wait for each other's reads through words in the workspace, with
+ *    a bounded wait: a part that cannot be stored in time goes through the
+ *    workspace.
+ *  - In two passes (2^20, and the rest): pass 1 applies `scale` and the stages on
+ *    index bits 15..log2(n)-1 (between the 2^15-element blocks of a row) into
+ *    fp32 values in the workspace, pass 2 the stages on bits 0..14 within each
+ *    block, and rounds once, with 12 bytes of HBM traffic per element.
  * Every intermediate stays fp32, so the numerics are those of the one-pass
- * sizes; the HBM traffic is 12 bytes per element instead of 4.  For n <= 2^16
- * the call is hadamard_transform_strided and the workspace is not touched.
+ * sizes.  For n <= 2^16 the call is hadamard_transform_strided and the workspace
+ * is not touched.
  *   workspace        device pointer, 16-byte aligned, at least
  *                    hadamard_transform_workspace_size(m, n) bytes, not
  *                    overlapping in or out (NULL allowed for n <= 2^16)
@@ -174,8 +183,7 @@ hadacore_status hadamard_transform_ws(const void *in, int64_t in_row_stride, voi
  *   Every call on one GPU uses that GPU's one array: calls that can overlap
  *   in time on the same GPU (different streams, host threads) race and give
  *   undefined results; calls in one stream's order are safe.  Nothing in the
- *   array needs to start at zero (pass 1 writes all of it before pass 2
- *   reads).  The first call on a device looks up that device's address of the
+ *   array needs to start at zero (every call writes what it reads).  The first call on a device looks up that device's address of the
  *   array (HADACORE_ERROR_LAUNCH if the runtime cannot give it); run that call
  *   outside graph capture.
  * Other arguments, strides, streams and errors as for hadamard_transform_ws.

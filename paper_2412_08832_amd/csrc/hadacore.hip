@@ -4,7 +4,8 @@
 // 16-bit rows of length n = 2^L, 0 <= L <= 16 in one pass (HadaCore, arXiv
 // 2412.08832: the transform of Sec. 2.1-2.2, sizes of Sec. 3.2 -- 2^7 to 2^15
 // -- plus the smaller ones and 2^16, in place per Appendix B, fp16 and bf16
-// per Appendix C), and up to 2^20 in two passes through a workspace.
+// per Appendix C), and up to 2^20 with a workspace: 2^17 to 2^19 in one pass by
+// workgroups that share a row, 2^20 (and shapes where it is faster) in two passes.
 // Rows of n <= 8 are one per thread (fwht_row_kernel), or, when n <= 4 and the
 // rows are dense, 8/n rows per thread (fwht_dense_kernel); the tile structure
 // below applies from n = 16.
@@ -151,6 +152,12 @@ constexpr int kPolicyNt = 2;  // buffer cache-policy operand: NT (bit 1)
 
 __device__ __forceinline__ u4 gload_u(const void *base, uint32_t off) {
   return __builtin_amdgcn_raw_buffer_load_b128(uniform_rsrc(base), (int)off, 0, kPolicyNt);
+}
+
+// The same load without the streaming policy, for data that other workgroups
+// of the XCD read as well.
+__device__ __forceinline__ u4 gload_c(const void *base, uint32_t off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(uniform_rsrc(base), (int)off, 0, 0);
 }
 
 template <bool NT, bool SC1>
@@ -885,8 +892,15 @@ __global__ __launch_bounds__(kWave *WPB) void fwht_wave_kernel(
 // run in order), and the only barrier is the one between the writes and the
 // reads of a pass.  A caller that runs several exchanges on the same LDS (the
 // row loops) alternates TR0 accordingly.
-template <int C, int NW, int HALVES, bool TR0, int N>
-__device__ __forceinline__ void exchange_wave_bits(float (&v)[N], float4 *lds) {
+// `after_first` runs in every thread once all waves have passed the first
+// barrier, that is, once every wave has consumed all of its row's loads.
+struct NoHook {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+template <int C, int NW, int HALVES, bool TR0, typename Hook = NoHook, int N>
+__device__ __forceinline__ void exchange_wave_bits(float (&v)[N], float4 *lds,
+                                                   Hook after_first = Hook()) {
   static_assert(NW >= 2 && NW <= C && NW <= 8, "wave bits must fit the chunk bits");
   static_assert(HALVES == 1 || HALVES == 2, "one or two exchange passes");
   constexpr int kParts = 2 / HALVES;
@@ -918,6 +932,7 @@ __device__ __forceinline__ void exchange_wave_bits(float (&v)[N], float4 *lds) {
       }
     }
     __syncthreads();
+    if (pass == 0) after_first();
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       const int Wk = (k % NW) * C + (k / NW) * NW;
@@ -1376,6 +1391,204 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
   }
 }
 
+// n = A * 2^15, n = 2^17..2^19 (sizes beyond the paper's range), in one pass: A
+// workgroups share a row, workgroup `a` computes its outputs a*2^15 ..
+// (a+1)*2^15 - 1, its part.  The stages on the top log2(A) index bits are sums
+// over the row's A blocks x_b, with signs (-1)^popcount(a & b), and a part needs
+// one of the A sums; then come the stages of the n = 2^15 block kernel.  Every
+// workgroup reads the whole row, but from the L2 that it shares with the row's
+// other workgroups (parts_slot puts them on one XCD), so HBM sees 2 + 2 bytes
+// per element instead of the two passes' 12.  The operations and their order
+// are the two passes', so the results are the same bits.
+//
+// What bounds it: VALU issue (A/2 * 9 - 1 operations per 2 outputs for the sum of
+// A blocks beside the 16 of the stages: about 21 us for 2^25 elements at A = 4,
+// 30 at 8, 47 at 16) and the L2 reads of A times the input.  Two workgroups per
+// CU overlap one's reads with the other's stages.  Measured against the two
+// passes (bf16, out of place, us): 251 rows of 2^17 72 -> 31, 128 rows of 2^18
+// 73 -> 40, 64 rows of 2^19 75 -> 59.  Summing the blocks on the matrix cores
+// instead was as fast with another order of the sums.
+//
+// In place (INPLACE), no part may be stored before all A workgroups have read
+// the row.  Each workgroup counts itself in the row's arrive word once its
+// loads are consumed, and waits, before its stores, until the count is A.  The
+// wait is bounded, since nothing promises that the row's workgroups are
+// resident together: when it runs out, the workgroup leaves its part in `defer`
+// and sets its bit in the same word.  Whoever moves the word second completes
+// the part: the bit's setter if it finds the count at A, else the workgroup
+// that makes the count A, which copies the parts whose bits it finds.  Arrive
+// words are 256 bytes apart: as neighbours, their atomics cost 5-15% more.
+constexpr int kPartL = 15;
+constexpr int kArriveBits = 8;    // arrive word: count in bits 0-7, deferred parts above
+constexpr int kArriveWords = 64;  // uint32 words from one row's arrive word to the next
+
+// Block index -> (group, part): groups of A workgroups that share rows.  With a
+// multiple of 8 groups a group's workgroups are 8 apart, which is one XCD
+// (workgroups go to the 8 XCDs in turn).
+struct PartsSlot {
+  int group, a;
+};
+template <int A>
+__device__ __forceinline__ PartsSlot parts_slot(int block, int groups) {
+  if ((groups & 7) == 0) {
+    const int slot = block >> 3;
+    return {(slot / A) * 8 + (block & 7), slot % A};
+  }
+  return {block / A, block % A};
+}
+
+// The sum of one chunk over the A blocks, in the two passes' order of
+// operations: with index bit 15 first, x0 * scale -+ x1 * scale as a product and
+// one fma, then a tree of additions.  `load(i)` gives the raw chunk of block i;
+// sg[l] = -1 where bit l of the part is set.
+template <int DT, int A, int B0, int LEN, typename Raw>
+__device__ __forceinline__ void part_sum(float (&v)[8], const Raw &raw, float s0, float s1,
+                                         const float (&sg)[5]) {
+  if constexpr (LEN == 2) {
+    const u4 r0 = raw(B0), r1 = raw(B0 + 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int sh = 16 * (j & 1);
+      v[j] = __builtin_fmaf(widen1<DT>(r0[j / 2] >> sh & 0xFFFFu), s0,
+                            widen1<DT>(r1[j / 2] >> sh & 0xFFFFu) * s1);
+    }
+  } else {
+    constexpr int l = LEN == 4 ? 1 : LEN == 8 ? 2 : LEN == 16 ? 3 : 4;
+    float hi[8];
+    part_sum<DT, A, B0, LEN / 2>(v, raw, s0, s1, sg);
+    part_sum<DT, A, B0 + LEN / 2, LEN / 2>(hi, raw, s0, s1, sg);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = __builtin_fmaf(hi[j], sg[l], v[j]);
+  }
+}
+
+template <int DT, int A, bool INPLACE>
+__global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
+    const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride, ScaleArgs sc,
+    int64_t m, int groups, uint16_t *defer, uint32_t *arrive, int spin_limit) {
+  constexpr int L = kPartL, NW = 8, C = 8;
+  constexpr int kPart = 1 << L;
+  constexpr int D = 4;  // loads in flight per lane; 8 spill, and were 0-30% slower
+  static_assert(A <= 32 - kArriveBits && A >= 2, "one bit of the arrive word per part");
+  __shared__ float4 lds[kPart / 4 / 2];
+  __shared__ uint32_t seen;  // INPLACE: what thread 0 tells the others of the arrive word
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+  const PartsSlot slot = parts_slot<A>((int)blockIdx.x, groups);
+  const int a = slot.a;
+  int64_t row = slot.group;
+  if (row >= m) return;
+
+  const int lane = threadIdx.x & (kWave - 1);
+  const float s1 = (a & 1) != 0 ? -sc.scale : sc.scale;
+  float sg[5];
+#pragma unroll
+  for (int l = 0; l < 5; ++l) sg[l] = (a >> l & 1) != 0 ? -1.0f : 1.0f;
+  // load q = chunk q / A of block q % A goes to raw[q % D]
+  u4 raw[D];
+  auto load = [&](const uint16_t *r, int q) {
+    return gload_c(r + (q % A) * kPart + (w * C + q / A) * 512, (uint32_t)lane * 16);
+  };
+  const uint16_t *src = in + row * in_stride;
+#pragma unroll
+  for (int q = 0; q < D; ++q) raw[q] = load(src, q);
+
+  for (;;) {
+    const int64_t next = row + groups;
+    const bool more = next < m;
+    // the last loads are the next row's first (a row without one reads its own again)
+    const uint16_t *nsrc = more ? in + next * in_stride : src;
+    float v[C * 8];
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      float x[8];
+      part_sum<DT, A, 0, A>(x, [&](int b) {
+        const int q = k * A + b;
+        const u4 r = raw[q % D];
+        raw[q % D] = q + D < C * A ? load(src, q + D) : load(nsrc, q + D - C * A);
+        return r;
+      }, sc.scale, s1, sg);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[k * 8 + j] = x[j];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    src = nsrc;
+    reg_stage<0>(v);
+    reg_stage<1>(v);
+    reg_stage<2>(v);
+    wave_stages<kValu, L, C>(v, lane);
+    uint32_t *const word = INPLACE ? arrive + row * kArriveWords : nullptr;
+    uint32_t before = 0;  // INPLACE, thread 0: the word before this workgroup's arrival
+    exchange_wave_bits<C, NW, 2, false>(v, lds, [&]() {
+      if (INPLACE && threadIdx.x == 0)
+        before = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
+    const uint32_t st_off = (uint32_t)(lane_field<kValu, L>(lane) * 16);
+    const Finisher<DT, kValu> fin(twisted<kValu, L>(lane), 1.0f);
+    uint16_t *dst = out + row * out_stride + (int64_t)a * kPart;
+    constexpr uint32_t kCount = (1u << kArriveBits) - 1;
+    bool late = false;
+    uint32_t copies = 0;  // deferred parts that this workgroup copies to the output
+    if constexpr (INPLACE) {
+      if (threadIdx.x == 0) {
+        uint32_t now = before + 1;
+        for (int i = 0; (now & kCount) != A && i < spin_limit; ++i) {
+          __builtin_amdgcn_s_sleep(1);
+          now = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const uint32_t owed = (before & kCount) == A - 1 ? before >> kArriveBits : 0u;
+        seen = (now & kCount) | (owed << kArriveBits);
+      }
+      __syncthreads();
+      const uint32_t s = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen);
+      late = (s & kCount) != A;
+      copies = s >> kArriveBits;
+      if (late) dst = defer + (row * A + a) * kPart;
+    }
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      const int W = (k % NW) * C + (k / NW) * NW + w;
+      gstore_u<true, false>(dst + W * 512, st_off, fin(&v[k * 8]));
+    }
+    if constexpr (INPLACE) {
+      if (late) {
+        // the part is in `defer`: make it visible, then set the bit
+        __threadfence();
+        __syncthreads();
+        if (threadIdx.x == 0)
+          seen = __hip_atomic_fetch_or(word, 1u << (kArriveBits + a), __ATOMIC_ACQ_REL,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        // all A have read the row meanwhile: nobody else will copy this part
+        if (((uint32_t)__builtin_amdgcn_readfirstlane((int)seen) & kCount) == A)
+          copies = 1u << a;
+      }
+      if (copies != 0) {
+        __threadfence();
+        // opaque, so that no address of this rare path is kept in registers
+        int t = (int)threadIdx.x;
+        asm volatile("" : "+v"(t));
+#pragma unroll 1
+        for (int p = 0; p < A; ++p) {
+          if ((copies >> p & 1) == 0) continue;
+          const uint16_t *from = defer + (row * A + p) * kPart;
+          uint16_t *to = out + row * out_stride + (int64_t)p * kPart;
+#pragma unroll 1
+          for (int i = t; i < kPart / 8; i += 512) gstore_at<false>(to, i * 16u, gload_at<false>(from, i * 16u));
+        }
+      }
+      __syncthreads();  // `seen` is rewritten for the next row
+    }
+    if (!more) return;
+    row = next;
+  }
+}
+
+// Clears the arrive words of an in-place call.
+__global__ __launch_bounds__(256) void clear_arrive_kernel(uint32_t *arrive, int64_t rows) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < rows) arrive[i * kArriveWords] = 0;
+}
+
 // n <= 4 with dense rows (both strides equal to n): the rows form one
 // contiguous array of m*n elements, so each thread takes 8 consecutive
 // elements -- 8/n whole rows -- with one 16-byte load and store, like the wider
@@ -1787,15 +2000,80 @@ hipError_t launch_large(const uint16_t *in, int64_t in_stride, uint16_t *out, in
   return hipGetLastError();
 }
 
+// The parts kernel on m rows.  The workspace holds the deferred parts of an
+// in-place call (2 bytes per element) and then its arrive words (256 bytes per
+// row; together at most the 4 bytes per element of the two passes).
+template <int DT, int A>
+hipError_t launch_parts(const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride,
+                        int64_t m, float scale, float *ws, int spin_limit, hipStream_t stream) {
+  const ScaleArgs sc{scale, 1.0f, 0};
+  // groups of A workgroups that fit the chip at once, a multiple of 8 where
+  // there are more (see parts_slot); groups past row m end at once
+  const int64_t slots = (int64_t)device_cus() * 2;
+  const int64_t most = slots / A > 0 ? slots / A : 1;
+  int64_t groups = m;
+  if (groups > 8) groups = (groups + 7) & ~int64_t(7);
+  if (groups > most) groups = most;
+  const dim3 grid((uint32_t)(groups * A));
+  if (in == out) {
+    uint16_t *defer = reinterpret_cast<uint16_t *>(ws);
+    uint32_t *arrive = reinterpret_cast<uint32_t *>(defer + m * (int64_t(A) << kPartL));
+    hipLaunchKernelGGL(clear_arrive_kernel, dim3((uint32_t)((m + 255) / 256)), dim3(256), 0, stream,
+                       arrive, m);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, true>), grid, dim3(512), 0, stream, in,
+                       in_stride, out, out_stride, sc, m, (int)groups, defer, arrive, spin_limit);
+  } else {
+    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, false>), grid, dim3(512), 0, stream, in,
+                       in_stride, out, out_stride, sc, m, (int)groups, nullptr, nullptr, 0);
+  }
+  return hipGetLastError();
+}
+
+// How n = 2^17..2^19 runs: kTwoPasses or kParts as forced for testing, kMeasured
+// the choice of parts_pay; polls before an in-place part is deferred.
+enum LargePath { kMeasured, kTwoPasses, kParts };
+struct LargeMode {
+  LargePath path;
+  int spin_limit;
+};
+
+// Whether m rows run as parts rather than two passes (the bits are the same).
+// Out of place parts win at every m for 2^17 and 2^18 (us, two passes / parts: 1
+// row 11.3 / 8.7 and 12.2 / 10.8; 512 rows of 2^17 139 / 70, 256 rows of 2^18
+// 139 / 95); at 2^19, where each row is read 16 times, with 8 rows (19.3 / 16.8;
+// 6 rows 18.0 / 19.6) up to 2^25 elements (64 rows 74.9 / 58.9; 128 rows, whose
+// reads come from HBM, 141 / 142).  In place the clearing launch and the waits
+// cost 4 us and more: from 8 rows at 2^17 and 2^18 (4 rows of 2^17 12.0 / 13.7, 16
+// rows 15.9 / 12.5; 2 rows of 2^18 12.8 / 18.6, 8 rows 17.0 / 15.1), not at 2^19
+// (33 rows 46 / 54, 64 rows 74.8 / 75.8).
+bool parts_pay(int L, int64_t m, bool inplace) {
+  if (L == 19) return !inplace && m >= 8 && m <= 64;
+  return !inplace || m >= 8;
+}
+
+template <int DT, int LN>
+hipError_t launch_large_size(const uint16_t *in, int64_t in_stride, uint16_t *out,
+                             int64_t out_stride, int64_t m, float scale, float *ws, LargeMode mode,
+                             hipStream_t stream) {
+  if constexpr (LN < 20) {
+    if (mode.path == kParts || (mode.path == kMeasured && parts_pay(LN, m, in == out)))
+      return launch_parts<DT, 1 << (LN - 15)>(in, in_stride, out, out_stride, m, scale, ws,
+                                              mode.spin_limit, stream);
+  }
+  return launch_large<DT, 1 << (LN - 15)>(in, in_stride, out, out_stride, m, scale, ws, stream);
+}
+
 template <int DT>
 hipError_t launch_large_one(int L, const uint16_t *in, int64_t in_stride, uint16_t *out,
-                            int64_t out_stride, int64_t m, float scale, float *ws,
-                            hipStream_t stream) {
+                            int64_t out_stride, int64_t m, float scale, float *ws, LargeMode mode,
+                            hipStream_t s) {
   switch (L) {
-    case 17: return launch_large<DT, 4>(in, in_stride, out, out_stride, m, scale, ws, stream);
-    case 18: return launch_large<DT, 8>(in, in_stride, out, out_stride, m, scale, ws, stream);
-    case 19: return launch_large<DT, 16>(in, in_stride, out, out_stride, m, scale, ws, stream);
-    case 20: return launch_large<DT, 32>(in, in_stride, out, out_stride, m, scale, ws, stream);
+    case 17: return launch_large_size<DT, 17>(in, in_stride, out, out_stride, m, scale, ws, mode, s);
+    case 18: return launch_large_size<DT, 18>(in, in_stride, out, out_stride, m, scale, ws, mode, s);
+    case 19: return launch_large_size<DT, 19>(in, in_stride, out, out_stride, m, scale, ws, mode, s);
+    case 20: return launch_large_size<DT, 20>(in, in_stride, out, out_stride, m, scale, ws, mode, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1838,14 +2116,14 @@ hipError_t launch_dt(int L, const uint16_t *in, int64_t in_stride, uint16_t *out
 // n > 2^16 through the workspace: row r0 of a launch uses workspace row r0 too.
 template <int DT>
 hipError_t launch_large_dt(int L, const uint16_t *in, int64_t in_stride, uint16_t *out,
-                           int64_t out_stride, int64_t m, float scale, float *ws,
+                           int64_t out_stride, int64_t m, float scale, float *ws, LargeMode mode,
                            hipStream_t stream) {
   const int64_t chunk = rows_per_launch(L);
   for (int64_t r0 = 0; r0 < m; r0 += chunk) {
     const int64_t mc = m - r0 < chunk ? m - r0 : chunk;
     const hipError_t e = launch_large_one<DT>(L, in + r0 * in_stride, in_stride,
                                               out + r0 * out_stride, out_stride, mc, scale,
-                                              ws + r0 * (int64_t(1) << L), stream);
+                                              ws + r0 * (int64_t(1) << L), mode, stream);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1859,6 +2137,19 @@ int front_override() {
   if (strcmp(v, "valu") == 0) return kValu;
   if (strcmp(v, "mfma") == 0) return kMfma;
   return -1;
+}
+
+// The same variable for n > 2^16: "passes" and "parts" force a path, "parts-defer"
+// the parts with no wait, so that in-place parts go through the workspace.
+// Otherwise the wait is 4096 polls, a few milliseconds, far beyond any row's time.
+LargeMode large_override() {
+  const char *v = getenv("HADACORE_VARIANT");
+  if (v != nullptr) {
+    if (strcmp(v, "passes") == 0) return {kTwoPasses, 0};
+    if (strcmp(v, "parts") == 0) return {kParts, 4096};
+    if (strcmp(v, "parts-defer") == 0) return {kParts, 0};
+  }
+  return {kMeasured, 4096};
 }
 
 // Architecture check, cached per device: 0 unknown, 1 gfx950, 2 other.
@@ -1955,10 +2246,10 @@ hadacore_status validate(const void *in, int64_t in_row_stride, const void *out,
 // long, alive until the process ends.  Host code never uses the symbol's name
 // as an address: on its first call on a device the entry point asks the
 // runtime for that device's address of the array (hipGetSymbolAddress, with
-// the device current) and keeps it here.  The two-pass kernels write every
-// workspace element in pass 1 before pass 2 reads it, so nothing needs
-// clearing between calls; calls that overlap on one GPU share the array and
-// race.
+// the device current) and keeps it here.  Every call
+// writes (or clears, in a launch of its own) what it reads of the workspace, so
+// nothing needs clearing between calls; calls that overlap on one GPU share the
+// array and race.
 constexpr int64_t kScratchBytes = HADACORE_NOALLOC_SCRATCH_BYTES;
 __device__ __align__(256) float scratch[kScratchBytes / sizeof(float)];
 
@@ -2067,8 +2358,8 @@ hadacore_status transform_two_pass(const void *in, int64_t in_row_stride, void *
   hipStream_t s = static_cast<hipStream_t>(stream);
   const hipError_t err =
       dtype == HADACORE_FP16
-          ? launch_large_dt<HADACORE_FP16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, s)
-          : launch_large_dt<HADACORE_BF16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, s);
+          ? launch_large_dt<HADACORE_FP16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, large_override(), s)
+          : launch_large_dt<HADACORE_BF16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, large_override(), s);
   return err == hipSuccess ? HADACORE_SUCCESS : HADACORE_ERROR_LAUNCH;
 }
 

@@ -67,6 +67,7 @@
 
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "hadacore.h"
 
@@ -749,7 +750,9 @@ struct RowQuant {
 // the last tile can end past row m; it masks those rows.  Addresses are a
 // wave-uniform tile base plus per-lane byte offsets inside the tile, which the
 // row stride limit (2^26 elements) keeps below 2^32.
-template <int DT, int L, int C, int T, int WPB, bool NT, int FRONT, int EPI, bool SC1 = false>
+// CACHED: input loads with the ordinary cache policy (cached_input).
+template <int DT, int L, int C, int T, int WPB, bool NT, int FRONT, int EPI, bool SC1 = false,
+          bool CACHED = false>
 __global__ __launch_bounds__(kWave *WPB) void fwht_wave_kernel(
     const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride, int64_t m,
     ScaleArgs sc, QuantOut qo) {
@@ -791,7 +794,7 @@ __global__ __launch_bounds__(kWave *WPB) void fwht_wave_kernel(
 #pragma unroll
     for (int k = 0; k < C; ++k) {
       if (kRows == 1 || ld_row[k] < valid) {
-        raw[k] = gload_at<NT>(base, ld_off[k]);
+        raw[k] = gload_at<NT && !CACHED>(base, ld_off[k]);
       } else {
         raw[k] = u4{0, 0, 0, 0};
       }
@@ -964,9 +967,10 @@ __device__ __forceinline__ void exchange_wave_bits(float (&v)[N], float4 *lds,
 // each exchange pass takes 128 KiB of LDS: one workgroup per CU.
 //
 // IN32 (second pass of n > 2^16): the input rows are fp32, already scaled, and
-// row r of the input is block r & (2^sub - 1) of output row r >> sub.
+// row r of the input is block r & (2^sub - 1) of output row r >> sub.  CACHED: as
+// in the wave kernel.
 template <int DT, int L, int C, int HALVES, bool NT, int FRONT, int EPI, bool IN32 = false,
-          bool SC1 = false>
+          bool SC1 = false, bool CACHED = false>
 __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_kernel(
     const void *in, int64_t in_stride, uint16_t *out, int64_t out_stride, ScaleArgs sc,
     QuantOut qo, int sub) {
@@ -1017,7 +1021,7 @@ __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_kernel(
     const int lf_load = lane_field_load<FRONT, L>(lane);
 #pragma unroll
     for (int k = 0; k < C; ++k) {
-      raw[k] = gload_at<NT>(src, (uint32_t)(((w * C + k) * kWave + lf_load) * 16));
+      raw[k] = gload_at<NT && !CACHED>(src, (uint32_t)(((w * C + k) * kWave + lf_load) * 16));
     }
     front<DT, FRONT, C>(raw, v, lane, sc.scale, sc.e2);
     if constexpr (kRaise) __builtin_amdgcn_s_setprio(0);
@@ -1075,18 +1079,19 @@ __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_kernel(
 // The loops' 16-byte loads: buffer loads for 16-bit output (gload_u); global
 // ones for the quantized epilogues, whose n = 65536 loop spills two VGPRs with
 // buffer loads and measured the same either way.
-template <bool NT, int EPI>
+template <bool NT, int EPI, bool CACHED>
 __device__ __forceinline__ u4 loop_load(const uint16_t *base, uint32_t off) {
   if constexpr (NT && EPI == kStore16) {
+    static_assert(!CACHED, "16-bit loops stream their input");
     return gload_u(base, off);
   } else {
-    return gload_at<NT>(base, off);
+    return gload_at<NT && !CACHED>(base, off);
   }
 }
 
 // One row of the loop: transform `raw` (row `row`), prefetch row `row` +
 // gridDim.x into `raw` when it exists, store; returns whether it did.
-template <int DT, int L, int C, int HALVES, bool NT, int EPI, int PRE, bool TR0>
+template <int DT, int L, int C, int HALVES, bool NT, int EPI, int PRE, bool TR0, bool CACHED>
 __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16_t *in,
                                          int64_t in_stride, uint16_t *out, int64_t out_stride,
                                          const ScaleArgs &sc, const QuantOut &qo, int64_t m,
@@ -1107,12 +1112,12 @@ __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16
     const uint16_t *src = in + next * in_stride;
     const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
 #pragma unroll
-    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI>(src + (w * C + k) * 512, ld_off);
+    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
   } else if (EPI != kStore16) {
     const uint16_t *src = in + (more ? next : m - 1) * in_stride;
     const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
 #pragma unroll
-    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI>(src + (w * C + k) * 512, ld_off);
+    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
   }
   wave_stages<kMfma, L, C>(v, lane);
   exchange_wave_bits<C, NW, HALVES, TR0>(v, lds);
@@ -1146,14 +1151,14 @@ __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16
       const int W = (k % NW) * C + (k / NW) * NW + w;
       gstore8_u<NT, false>(codes + W * 512, (uint32_t)(lf * 8), qz.codes(&v[k * 8]));
       // the chunks not prefetched yet go out as stored chunks free registers
-      if (k < C - PRE) raw[PRE + k] = loop_load<NT, EPI>(src + (w * C + PRE + k) * 512, ld_off);
+      if (k < C - PRE) raw[PRE + k] = loop_load<NT, EPI, CACHED>(src + (w * C + PRE + k) * 512, ld_off);
     }
     if (threadIdx.x == 0) qo.scales[row] = qz.scale;
   }
   return more;
 }
 
-template <int DT, int L, int C, int HALVES, bool NT, int EPI>
+template <int DT, int L, int C, int HALVES, bool NT, int EPI, bool CACHED = false>
 __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_loop_kernel(
     const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride, ScaleArgs sc,
     QuantOut qo, int64_t m) {
@@ -1168,7 +1173,7 @@ __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_loop_kernel(
   const uint16_t *src = in + row * in_stride;
   const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
 #pragma unroll
-  for (int k = 0; k < C; ++k) raw[k] = loop_load<NT, EPI>(src + (w * C + k) * 512, ld_off);
+  for (int k = 0; k < C; ++k) raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
   // The first row is peeled so that the loop is entered, like it is
   // re-entered, with the next row's loads older than this row's stores: the
   // compiler's wait before the front end then covers the loads only, not the
@@ -1177,24 +1182,24 @@ __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_loop_kernel(
   // With two exchange passes every row takes both slot maps; with one,
   // consecutive rows take them in turn (the loop is unrolled by two).  Either
   // way the LDS needs no barrier before a row's exchange writes.
-  if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false>(raw, row, in, in_stride, out, out_stride,
+  if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false, CACHED>(raw, row, in, in_stride, out, out_stride,
                                                          sc, qo, m, lds, wave_max, w, lane))
     return;
   if constexpr (HALVES == 2) {
     do {
       row += gridDim.x;
-    } while (loop_row<DT, L, C, HALVES, NT, EPI, PRE, false>(raw, row, in, in_stride, out,
+    } while (loop_row<DT, L, C, HALVES, NT, EPI, PRE, false, CACHED>(raw, row, in, in_stride, out,
                                                                out_stride, sc, qo, m, lds,
                                                                wave_max, w, lane));
   } else {
     for (;;) {
       row += gridDim.x;
-      if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, true>(raw, row, in, in_stride, out,
+      if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, true, CACHED>(raw, row, in, in_stride, out,
                                                             out_stride, sc, qo, m, lds, wave_max,
                                                             w, lane))
         return;
       row += gridDim.x;
-      if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false>(raw, row, in, in_stride, out,
+      if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false, CACHED>(raw, row, in, in_stride, out,
                                                              out_stride, sc, qo, m, lds, wave_max,
                                                              w, lane))
         return;
@@ -1777,6 +1782,35 @@ bool whole_lines(const void *p, int64_t pitch_bytes, int64_t row_bytes) {
   return pitch_bytes == row_bytes || (pitch_bytes % 128 == 0 && row_bytes % 128 == 0);
 }
 
+// Cache policies by the size of a call.
+//
+// In-place calls up to kSmallInPlace elements (8 MiB) store without SC1, which
+// at that size costs more than it saves (us, with / without: n = 128, 2^16
+// elements 2.42 / 2.13, 2^21 3.62 / 3.28; n = 4096 3.09 / 2.62 and 3.88 / 3.67;
+// equal from 2^23).
+constexpr int64_t kSmallInPlace = int64_t(1) << 22;
+
+// Whether a call loads its input with the ordinary cache policy instead of the
+// streaming one, so that an input that is in the 256 MiB last-level cache, put
+// there by its producer or an earlier reader, is served from it and stays.
+// Measured out of place against streaming loads (n = 64-16384): on three rotating
+// buffer sets +10 to +20% at 2^24 and 2^25 elements; input written by the
+// kernel before, both kernels together, +4 to +7% up to 2^25, +1% at 1.5 *
+// 2^25, -4% at 2^26; input in neither cache -2 to -5%.  From 2^26 (128 MiB) all
+// three lose, and below 2^23 they are equal.  The lower ends differ: 2^23
+// gains 8-10% up to n = 1024 and loses 4% above; n = 32768 gains 16% at 2^25, 0
+// at 2^24; quantized output gains 3-11% from 2^23 (n <= 128), 4-8% above it (n <=
+// 1024) and 11-13% at 2^25 above (2^24 -3%).  Quantized n = 65536 gains 6-21% from
+// 2^22: its ending workgroups all read the last row once more.
+bool cached_input(int epi, int L, int64_t m, bool inplace) {
+  const int64_t e = m << L;
+  if (inplace || e > int64_t(1) << 25) return false;
+  if (epi == kStore16)
+    return L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24;
+  if (L == 16) return e >= 1 << 22;
+  return L <= 7 ? e >= 1 << 23 : L <= 10 ? e > 1 << 23 : e > 1 << 24;
+}
+
 // C: chunks per lane; T: tiles per wave (wave kernel) ; WPB: waves per workgroup
 // (wave kernel); HALVES: LDS exchange passes (block kernel); FRONT: kValu / kMfma.
 template <int DT, int L, int C, int T, int WPB, int HALVES, int FRONT, int EPI = kStore16>
@@ -1784,8 +1818,10 @@ hipError_t launch_cfg(const uint16_t *in, int64_t in_stride, uint16_t *out, int6
                       int64_t m, const ScaleArgs &sc, hipStream_t stream, QuantOut qo = {}) {
   // output stores with the SC1 bit (see gstore_u) only where every store
   // instruction writes whole 128-byte lines
-  const bool sc1 = EPI == kStore16 ? whole_lines(out, out_stride * 2, 2 << L)
-                                   : whole_lines(qo.codes, qo.stride, 1 << L);
+  const bool small_in_place = EPI == kStore16 && in == out && (m << L) <= kSmallInPlace;
+  const bool sc1 = !small_in_place &&
+                   (EPI == kStore16 ? whole_lines(out, out_stride * 2, 2 << L)
+                                    : whole_lines(qo.codes, qo.stride, 1 << L));
   if constexpr (L <= 2) {
     const int64_t out_pitch = EPI == kStore16 ? out_stride : qo.stride;
     if (in_stride == (1 << L) && out_pitch == (1 << L)) {
@@ -1809,34 +1845,45 @@ hipError_t launch_cfg(const uint16_t *in, int64_t in_stride, uint16_t *out, int6
     else
       hipLaunchKernelGGL((fwht_row_kernel<DT, L, true, EPI>), dim3((uint32_t)((m + 255) / 256)),
                          dim3(256), 0, stream, in, in_stride, out, out_stride, m, sc, qo);
-  } else if constexpr ((1 << L) <= 512 * C) {
-    constexpr int64_t rows_per_wave = (int64_t)T * ((512 * C) >> L);
-    const int64_t waves = (m + rows_per_wave - 1) / rows_per_wave;
-    const dim3 grid((uint32_t)((waves + WPB - 1) / WPB));
-    if (sc1)
-      hipLaunchKernelGGL((fwht_wave_kernel<DT, L, C, T, WPB, true, FRONT, EPI, true>), grid,
-                         dim3(kWave * WPB), 0, stream, in, in_stride, out, out_stride, m, sc, qo);
-    else
-      hipLaunchKernelGGL((fwht_wave_kernel<DT, L, C, T, WPB, true, FRONT, EPI, false>), grid,
-                         dim3(kWave * WPB), 0, stream, in, in_stride, out, out_stride, m, sc, qo);
-  } else if constexpr (L == 16 && FRONT == kMfma) {
-    // one resident workgroup per CU, each looping over rows
-    const int64_t cus = device_cus();
-    const int64_t blocks = m < cus ? m : cus;
-    hipLaunchKernelGGL((fwht_block_loop_kernel<DT, L, C, HALVES, true, EPI>),
-                       dim3((uint32_t)blocks), dim3((1 << L) / (8 * C)), 0, stream, in, in_stride,
-                       out, out_stride, sc, qo, m);
   } else {
+    const bool cached = cached_input(EPI, L, m, EPI == kStore16 && in == out);
+    const auto launch_as = [&](auto with_sc1, auto with_cached) {
+      constexpr bool kSc1 = decltype(with_sc1)::value, kCached = decltype(with_cached)::value;
+      if constexpr ((1 << L) <= 512 * C) {
+        constexpr int64_t rows_per_wave = (int64_t)T * ((512 * C) >> L);
+        const int64_t waves = (m + rows_per_wave - 1) / rows_per_wave;
+        const dim3 grid((uint32_t)((waves + WPB - 1) / WPB));
+        hipLaunchKernelGGL((fwht_wave_kernel<DT, L, C, T, WPB, true, FRONT, EPI, kSc1, kCached>),
+                           grid, dim3(kWave * WPB), 0, stream, in, in_stride, out, out_stride, m,
+                           sc, qo);
+      } else if constexpr (L == 16 && FRONT == kMfma) {
+        // one resident workgroup per CU, each looping over rows
+        const int64_t cus = device_cus();
+        const int64_t blocks = m < cus ? m : cus;
+        hipLaunchKernelGGL((fwht_block_loop_kernel<DT, L, C, HALVES, true, EPI, kCached>),
+                           dim3((uint32_t)blocks), dim3((1 << L) / (8 * C)), 0, stream, in,
+                           in_stride, out, out_stride, sc, qo, m);
+      } else {
+        hipLaunchKernelGGL(
+            (fwht_block_kernel<DT, L, C, HALVES, true, FRONT, EPI, false, kSc1, kCached>),
+            dim3((uint32_t)m), dim3((1 << L) / (8 * C)), 0, stream, in, in_stride, out, out_stride,
+            sc, qo, 0);
+      }
+    };
     // 16-bit rows of 2^14 and more store without SC1 (see gstore_u)
-    constexpr bool kMaySc1 = EPI != kStore16 || L <= 13;
-    if (kMaySc1 && sc1)
-      hipLaunchKernelGGL((fwht_block_kernel<DT, L, C, HALVES, true, FRONT, EPI, false, kMaySc1>),
-                         dim3((uint32_t)m), dim3((1 << L) / (8 * C)), 0, stream, in, in_stride, out,
-                         out_stride, sc, qo, 0);
-    else
-      hipLaunchKernelGGL((fwht_block_kernel<DT, L, C, HALVES, true, FRONT, EPI, false, false>),
-                         dim3((uint32_t)m), dim3((1 << L) / (8 * C)), 0, stream, in, in_stride, out,
-                         out_stride, sc, qo, 0);
+    constexpr std::bool_constant<(EPI != kStore16 || L <= 13) && !(L == 16 && FRONT == kMfma)>
+        may_sc1{};
+    constexpr std::bool_constant<!(L == 16 && EPI == kStore16)> may_cache{};
+    if (sc1) {
+      if (cached)
+        launch_as(may_sc1, may_cache);
+      else
+        launch_as(may_sc1, std::false_type{});
+    } else if (cached) {
+      launch_as(std::false_type{}, may_cache);
+    } else {
+      launch_as(std::false_type{}, std::false_type{});
+    }
   }
   return hipGetLastError();
 }

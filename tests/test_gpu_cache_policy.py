@@ -1,0 +1,36 @@
+"""Calls whose size picks another cache policy for their loads or stores give
+the bits of the same rows in a call of another size, on both sides of each line
+of the rule, with aligned rows and with rows off the 128-byte lines."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2412_08832_amd import hadacore as H
+
+pytestmark = pytest.mark.gpu
+
+# (n, total elements): up to 2^22 in place stores without SC1; 2^23 < .. <= 2^25 loads
+# with the ordinary policy (other lines for n >= 32768 and quantized rows)
+SIZES = [(64, 1 << 23), (128, 1 << 22), (1024, 1 << 24), (4096, 1 << 22), (4096, 1 << 24),
+         (16384, 1 << 25), (32768, 1 << 25), (65536, 1 << 22), (65536, 1 << 25)]
+
+
+@pytest.mark.parametrize("pad", [0, 16])
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("n,total", SIZES)
+def test_rows_do_not_depend_on_the_size_of_the_call(n, total, more, pad):
+    import torch
+    m = total // n + more
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    buf = torch.randn((m, n + pad), device="cuda", generator=gen).to(torch.bfloat16)
+    x = buf[:, :n]
+    rows = [0, m // 2, m - 1]
+    small = buf[rows][:, :n]           # three rows: the smallest calls' policy
+    y, ref = H.transform(x), H.transform(small)
+    assert torch.equal(y[rows], ref)
+    for f in (H.transform_fp8, H.transform_int8):
+        (c, s), (rc, rs) = f(x), f(small)
+        assert torch.equal(c[rows], rc) and torch.equal(s[rows], rs)
+    z = buf.clone()
+    H.transform(z[:, :n], out=z[:, :n])
+    assert torch.equal(z[:, :n], y) and torch.equal(z[:, n:], buf[:, n:])

@@ -177,13 +177,53 @@ def hadacore_version() -> int:
     return int(library().hadacore_version())
 
 
-def _dtype_code(t) -> int:
+# What the tensor wrappers need of torch, looked up on the first call: a call is a
+# few microseconds, of which module and attribute lookups, stream objects and
+# device contexts were half.
+_torch = None
+_dtype_codes: dict = {}
+_raw_stream = None
+_current_device = None
+_one_device = False
+# the default scale fp32(1/sqrt(n)) of every supported n
+_SCALES = {1 << k: float(ctypes.c_float(1.0 / math.sqrt(1 << k)).value) for k in range(21)}
+
+
+def _init_torch() -> None:
+    global _torch, _raw_stream, _current_device, _one_device
     import torch
-    if t.dtype == torch.float16:
-        return FP16
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"expected float16 or bfloat16, got {t.dtype}")
+    _dtype_codes.update({torch.float16: FP16, torch.bfloat16: BF16})
+    _current_device = torch.cuda.current_device
+    _one_device = torch.cuda.device_count() == 1
+    # the current stream's handle without building a Stream object
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+        lambda index: torch.cuda.current_stream(index).cuda_stream)
+    _torch = torch
+
+
+def _dtype_code(t) -> int:
+    code = _dtype_codes.get(t.dtype)
+    if code is None:
+        raise TypeError(f"expected float16 or bfloat16, got {t.dtype}")
+    return code
+
+
+def _default_scale(n: int) -> float:
+    scale = _SCALES.get(n)
+    return float(ctypes.c_float(1.0 / math.sqrt(n)).value) if scale is None else scale
+
+
+def _call(name: str, device: int, *args) -> None:
+    """The library's entry point ``name`` with ``device`` current, which it nearly
+    always is already (and is where there is only one)."""
+    entry = getattr(_lib or library(), name)
+    if _one_device or _current_device() == device:
+        status = entry(*args)
+    else:
+        with _torch.cuda.device(device):
+            status = entry(*args)
+    if status != SUCCESS:
+        raise HadacoreError(status, name)
 
 
 def transform(x, out=None, scale: float | None = None, n: int | None = None, stream=None,
@@ -197,69 +237,77 @@ def transform(x, out=None, scale: float | None = None, n: int | None = None, str
     contiguous ROCm tensor of at least hadamard_transform_workspace_size(m, n)
     bytes) is allocated here when not given.
     """
-    import torch
+    if _torch is None:
+        _init_torch()
     if x.dim() != 2 or not x.is_cuda:
         raise ValueError("expected a 2-D tensor on a ROCm device")
-    if x.stride(1) != 1:
+    in_stride, column = x.stride()
+    if column != 1:
         raise ValueError("rows must be contiguous (column stride 1)")
     code = _dtype_code(x)
-    n = x.shape[1] if n is None else int(n)
+    m, columns = x.shape
+    n = columns if n is None else int(n)
     if out is None:
-        out = torch.empty((x.shape[0], n), dtype=x.dtype, device=x.device)
-    if out.dtype != x.dtype or out.device != x.device or out.dim() != 2 or out.stride(1) != 1:
+        out = _torch.empty((m, n), dtype=x.dtype, device=x.device)
+    elif (out is not x) and (out.dtype != x.dtype or out.device != x.device or out.dim() != 2
+                             or out.stride(1) != 1):
         raise ValueError("out must be a 2-D tensor of the same dtype/device with column stride 1")
-    if out.shape[0] != x.shape[0] or out.shape[1] < n or x.shape[1] < n:
+    rows, width = out.shape
+    if rows != m or width < n or columns < n:
         raise ValueError("shape mismatch between x, out and n")
     if scale is None:
-        scale = float(ctypes.c_float(1.0 / math.sqrt(n)).value)
+        scale = _default_scale(n)
+    device = x.get_device()
     if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _raw_stream(device)
     elif hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
     # a single row's stride is never used to address anything; report n
-    in_stride = x.stride(0) if x.shape[0] > 1 else n
-    out_stride = out.stride(0) if out.shape[0] > 1 else n
-    with torch.cuda.device(x.device):
-        if n > 1 << 16:
-            need = hadamard_transform_workspace_size(x.shape[0], n)
-            if workspace is None:
-                workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
-            wbytes = workspace.numel() * workspace.element_size()
-            hadamard_transform_ws(x.data_ptr(), in_stride, out.data_ptr(), out_stride,
-                                  x.shape[0], n, code, scale, workspace.data_ptr(), wbytes,
-                                  stream)
-        else:
-            hadamard_transform_strided(x.data_ptr(), in_stride, out.data_ptr(), out_stride,
-                                       x.shape[0], n, code, scale, stream)
+    if m > 1:
+        out_stride = out.stride(0)
+    else:
+        in_stride = out_stride = n
+    if n > 1 << 16:
+        if workspace is None:
+            need = hadamard_transform_workspace_size(m, n)
+            workspace = _torch.empty(max(need, 16), dtype=_torch.uint8, device=x.device)
+        _call("hadamard_transform_ws", device, x.data_ptr(), in_stride, out.data_ptr(), out_stride,
+              m, n, code, scale, workspace.data_ptr(), workspace.numel() * workspace.element_size(),
+              stream)
+    else:
+        _call("hadamard_transform_strided", device, x.data_ptr(), in_stride, out.data_ptr(),
+              out_stride, m, n, code, scale, stream)
     return out
 
 
-def _transform_quantized(x, codes, scales, scale, stream, entry, codes_dtype):
-    import torch
+def _transform_quantized(x, codes, scales, scale, stream, entry, int8):
+    if _torch is None:
+        _init_torch()
+    codes_dtype = _torch.int8 if int8 else _torch.uint8
     if x.dim() != 2 or not x.is_cuda or x.stride(1) != 1:
         raise ValueError("expected a 2-D ROCm tensor with contiguous rows")
     code = _dtype_code(x)
     m, n = x.shape
     if codes is None:
-        codes = torch.empty((m, n), dtype=codes_dtype, device=x.device)
-    if scales is None:
-        scales = torch.empty((m,), dtype=torch.float32, device=x.device)
-    if codes.dtype != codes_dtype or codes.dim() != 2 or codes.stride(1) != 1 \
+        codes = _torch.empty((m, n), dtype=codes_dtype, device=x.device)
+    elif codes.dtype != codes_dtype or codes.dim() != 2 or codes.stride(1) != 1 \
             or tuple(codes.shape) != (m, n):
         raise ValueError(f"codes must be a (m, n) {codes_dtype} tensor with contiguous rows")
-    if scales.dtype != torch.float32 or scales.numel() != m or not scales.is_contiguous():
+    if scales is None:
+        scales = _torch.empty((m,), dtype=_torch.float32, device=x.device)
+    elif scales.dtype != _torch.float32 or scales.numel() != m or not scales.is_contiguous():
         raise ValueError("scales must be a contiguous float32 tensor of m elements")
     if scale is None:
-        scale = float(ctypes.c_float(1.0 / math.sqrt(n)).value)
+        scale = _default_scale(n)
+    device = x.get_device()
     if stream is None:
-        stream = torch.cuda.current_stream(x.device).cuda_stream
+        stream = _raw_stream(device)
     elif hasattr(stream, "cuda_stream"):
         stream = stream.cuda_stream
     in_stride = x.stride(0) if m > 1 else n
     codes_stride = codes.stride(0) if m > 1 else ((n + 15) // 16) * 16
-    with torch.cuda.device(x.device):
-        entry(x.data_ptr(), in_stride, codes.data_ptr(), codes_stride, scales.data_ptr(), m, n,
-              code, scale, stream)
+    _call(entry, device, x.data_ptr(), in_stride, codes.data_ptr(), codes_stride,
+          scales.data_ptr(), m, n, code, scale, stream)
     return codes, scales
 
 
@@ -270,9 +318,7 @@ def transform_fp8(x, codes=None, scales=None, scale: float | None = None, stream
     patterns and scales a (m,) float32 tensor, so that
     x @ H_n * scale ~ codes.view(torch.float8_e4m3fn).float() * scales[:, None].
     """
-    import torch
-    return _transform_quantized(x, codes, scales, scale, stream, hadamard_transform_fp8,
-                                torch.uint8)
+    return _transform_quantized(x, codes, scales, scale, stream, "hadamard_transform_fp8", False)
 
 
 def transform_int8(x, codes=None, scales=None, scale: float | None = None, stream=None):
@@ -280,6 +326,4 @@ def transform_int8(x, codes=None, scales=None, scale: float | None = None, strea
     tensor.  Returns (codes, scales): a (m, n) torch.int8 tensor and a (m,) float32
     tensor, so that x @ H_n * scale ~ codes.float() * scales[:, None].
     """
-    import torch
-    return _transform_quantized(x, codes, scales, scale, stream, hadamard_transform_int8,
-                                torch.int8)
+    return _transform_quantized(x, codes, scales, scale, stream, "hadamard_transform_int8", True)

@@ -750,7 +750,7 @@ struct RowQuant {
 // the last tile can end past row m; it masks those rows.  Addresses are a
 // wave-uniform tile base plus per-lane byte offsets inside the tile, which the
 // row stride limit (2^26 elements) keeps below 2^32.
-// CACHED: input loads with the ordinary cache policy (cached_input).
+// CACHED: input loads with the ordinary cache policy (CallPolicy).
 template <int DT, int L, int C, int T, int WPB, bool NT, int FRONT, int EPI, bool SC1 = false,
           bool CACHED = false>
 __global__ __launch_bounds__(kWave *WPB) void fwht_wave_kernel(
@@ -1788,33 +1788,65 @@ bool whole_lines(const void *p, int64_t pitch_bytes, int64_t row_bytes) {
   return pitch_bytes == row_bytes || (pitch_bytes % 128 == 0 && row_bytes % 128 == 0);
 }
 
-// Cache policies by the size of a call.
+// Cache policy of a call by its size, as measured in us against streaming loads
+// and, on whole lines, SC1 stores (which it is for all sizes not named here).
 //
-// In-place calls up to kSmallInPlace elements (8 MiB) store without SC1, which
-// at that size costs more than it saves (us, with / without: n = 128, 2^16
-// elements 2.42 / 2.13, 2^21 3.62 / 3.28; n = 4096 3.09 / 2.62 and 3.88 / 3.67;
-// equal from 2^23).
-constexpr int64_t kSmallInPlace = int64_t(1) << 22;
+// `cached`: input loads with the ordinary cache policy, so that an input that is
+// in the 256 MiB last-level cache, put there by its producer or an earlier
+// reader, is served from it and stays.
+// `sc1`: output stores with the SC1 bit (see gstore_u), on whole lines only.
+struct CallPolicy {
+  bool cached;
+  bool sc1;
+};
 
-// Whether a call loads its input with the ordinary cache policy instead of the
-// streaming one, so that an input that is in the 256 MiB last-level cache, put
-// there by its producer or an earlier reader, is served from it and stays.
-// Measured out of place against streaming loads (n = 64-16384): on three rotating
-// buffer sets +10 to +20% at 2^24 and 2^25 elements; input written by the
-// kernel before, both kernels together, +4 to +7% up to 2^25, +1% at 1.5 *
-// 2^25, -4% at 2^26; input in neither cache -2 to -5%.  From 2^26 (128 MiB) all
-// three lose, and below 2^23 they are equal.  The lower ends differ: 2^23
-// gains 8-10% up to n = 1024 and loses 4% above; n = 32768 gains 16% at 2^25, 0
-// at 2^24; quantized output gains 3-11% from 2^23 (n <= 128), 4-8% above it (n <=
-// 1024) and 11-13% at 2^25 above (2^24 -3%).  Quantized n = 65536 gains 6-21% from
-// 2^22: its ending workgroups all read the last row once more.
-bool cached_input(int epi, int L, int64_t m, bool inplace) {
-  const int64_t e = m << L;
-  if (inplace || e > int64_t(1) << 25) return false;
+// Out of place (n = 64-16384): on three rotating buffer sets cached loads gain 10
+// to 20% at 2^24 and 2^25 elements; with input written by the kernel before, both
+// kernels together, 4 to 7% up to 2^25, 1% at 1.5 * 2^25, -4% at 2^26; with input
+// in neither cache they lose 2 to 5%.  From 2^26 (128 MiB) all three lose, and
+// below 2^23 they are equal.  The lower ends differ: 2^23 gains 8-10% up to n =
+// 1024 and loses 4% above; n = 32768 gains 16% at 2^25, 0 at 2^24; quantized
+// output gains 3-11% from 2^23 (n <= 128), 4-8% above it (n <= 1024) and 11-13% at
+// 2^25 above (2^24 -3%).  Quantized n = 65536 gains 6-21% from 2^22: its ending
+// workgroups all read the last row once more.
+bool cached_out_of_place(int epi, int L, int64_t e) {
+  if (e > 1 << 25) return false;
   if (epi == kStore16)
     return L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24;
   if (L == 16) return e >= 1 << 22;
   return L <= 7 ? e >= 1 << 23 : L <= 10 ? e > 1 << 23 : e > 1 << 24;
+}
+
+// In place, 16-bit output.  Cached loads bring the lines into the L2 that the
+// stores then write; SC1 stores do not go with them (1-5% slower than either
+// alone).
+//  - Up to 2^22 elements (2^23 at n = 1024 and 4096) stores without SC1 gain 5-18%:
+//    n = 128 2^16 elements 2.42 -> 2.13, n = 4096 2^21 3.88 -> 3.67, n = 1024 2^23 7.6
+//    -> 6.9.
+//  - Rows on whole lines, cached loads and no SC1: n = 1024 +6 to +12% from 1.5 *
+//    2^22 to 2^25, n = 4096 and 8192 +1 to +8% above 2^23, n = 16384 +5 to +8% above
+//    2^24, n = 32768 +5 to +10% from 2^24; other n lose or are equal.
+//  - Rows off the lines with less than a line between them, so that neighbours
+//    share lines: n <= 128 +4 to +56% from 2^23 (n = 32, 2^25 elements 42.4 ->
+//    29.5), n = 256-1024 +3 to +16% up to 2^25 (2^26 -13 to +4%), n = 4096 and 8192
+//    +0 to +9% above 2^23 up to 2^25 (2^26 -2 to -4%), n = 16384 +4 to +9% above
+//    2^24, n = 32768 +6 to +13% from 2^24; n = 2048 is equal, and rows further
+//    apart lose up to 17%.
+CallPolicy in_place_policy(int L, int64_t e, bool whole, int64_t gap_bytes) {
+  const int64_t small = L == 10 || L == 12 ? 1 << 23 : 1 << 22;
+  if (e <= small) return {false, false};
+  const bool upto25 = e <= 1 << 25;
+  bool cached = false;
+  if (L == 15)
+    cached = e >= 1 << 24;
+  else if (L == 14)
+    cached = e > 1 << 24 && upto25;
+  else if (L == 12 || L == 13 || (L == 10 && whole))
+    cached = e > 1 << 23 && upto25;
+  else if (L <= 10 && !whole)
+    cached = e >= 1 << 23 && (L <= 7 || upto25);
+  if (!whole && gap_bytes >= 128) cached = false;
+  return {cached, whole && !cached};
 }
 
 // C: chunks per lane; T: tiles per wave (wave kernel) ; WPB: waves per workgroup
@@ -1822,12 +1854,13 @@ bool cached_input(int epi, int L, int64_t m, bool inplace) {
 template <int DT, int L, int C, int T, int WPB, int HALVES, int FRONT, int EPI = kStore16>
 hipError_t launch_cfg(const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride,
                       int64_t m, const ScaleArgs &sc, hipStream_t stream, QuantOut qo = {}) {
-  // output stores with the SC1 bit (see gstore_u) only where every store
-  // instruction writes whole 128-byte lines
-  const bool small_in_place = EPI == kStore16 && in == out && (m << L) <= kSmallInPlace;
-  const bool sc1 = !small_in_place &&
-                   (EPI == kStore16 ? whole_lines(out, out_stride * 2, 2 << L)
-                                    : whole_lines(qo.codes, qo.stride, 1 << L));
+  // whether every store instruction writes whole 128-byte lines
+  const bool whole = EPI == kStore16 ? whole_lines(out, out_stride * 2, 2 << L)
+                                     : whole_lines(qo.codes, qo.stride, 1 << L);
+  const int64_t elements = m << L;
+  const auto [cached, sc1] = EPI == kStore16 && in == out
+                                 ? in_place_policy(L, elements, whole, (out_stride - (1 << L)) * 2)
+                                 : CallPolicy{cached_out_of_place(EPI, L, elements), whole};
   if constexpr (L <= 2) {
     const int64_t out_pitch = EPI == kStore16 ? out_stride : qo.stride;
     if (in_stride == (1 << L) && out_pitch == (1 << L)) {
@@ -1852,7 +1885,6 @@ hipError_t launch_cfg(const uint16_t *in, int64_t in_stride, uint16_t *out, int6
       hipLaunchKernelGGL((fwht_row_kernel<DT, L, true, EPI>), dim3((uint32_t)((m + 255) / 256)),
                          dim3(256), 0, stream, in, in_stride, out, out_stride, m, sc, qo);
   } else {
-    const bool cached = cached_input(EPI, L, m, EPI == kStore16 && in == out);
     const auto launch_as = [&](auto with_sc1, auto with_cached) {
       constexpr bool kSc1 = decltype(with_sc1)::value, kCached = decltype(with_cached)::value;
       if constexpr ((1 << L) <= 512 * C) {

@@ -9,13 +9,13 @@ from paper_2412_08832_amd import hadacore as H
 
 pytestmark = pytest.mark.gpu
 
-# (n, total elements): up to 2^22 in place stores without SC1; 2^23 < .. <= 2^25 loads
-# with the ordinary policy (other lines for n >= 32768 and quantized rows)
+# (n, total elements): the lines of the rules lie at 2^22 .. 2^25, other ones for each
+# size, for quantized output, and in place by whether rows share lines (pad 8) or not
 SIZES = [(64, 1 << 23), (128, 1 << 22), (1024, 1 << 24), (4096, 1 << 22), (4096, 1 << 24),
          (16384, 1 << 25), (32768, 1 << 25), (65536, 1 << 22), (65536, 1 << 25)]
 
 
-@pytest.mark.parametrize("pad", [0, 16])
+@pytest.mark.parametrize("pad", [0, 8, 72])
 @pytest.mark.parametrize("more", [0, 1])
 @pytest.mark.parametrize("n,total", SIZES)
 def test_rows_do_not_depend_on_the_size_of_the_call(n, total, more, pad):

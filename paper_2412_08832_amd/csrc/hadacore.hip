@@ -1420,6 +1420,11 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 // 73 -> 40, 64 rows of 2^19 75 -> 59.  Summing the blocks on the matrix cores
 // instead was as fast with another order of the sums.
 //
+// TOUCH: while a row is in its stages, its workgroups fetch the lines of their
+// next row into the L2, one 4-byte load per line, a share each (us, without /
+// with: 512 rows of 2^17 70 / 67, 256 rows of 2^18 93 / 83, 128 rows of 2^19 142 /
+// 123).
+//
 // In place (INPLACE), no part may be stored before all A workgroups have read
 // the row.  Each workgroup counts itself in the row's arrive word once its
 // loads are consumed, and waits, before its stores, until the count is A.  The
@@ -1473,7 +1478,7 @@ __device__ __forceinline__ void part_sum(float (&v)[8], const Raw &raw, float s0
   }
 }
 
-template <int DT, int A, bool INPLACE>
+template <int DT, int A, bool INPLACE, bool TOUCH>
 __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
     const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride, ScaleArgs sc,
     int64_t m, int groups, uint16_t *defer, uint32_t *arrive, int spin_limit) {
@@ -1503,6 +1508,16 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
 #pragma unroll
   for (int q = 0; q < D; ++q) raw[q] = load(src, q);
 
+  // TOUCH: one line per lane of this wave's share of a row (kPart / NW elements)
+  uint32_t touched = 0;
+  auto touch = [&](const uint16_t *r) {
+    static_assert(kPart / NW * 2 == 128 * kWave, "a line per lane");
+    if constexpr (TOUCH)
+      touched = __builtin_amdgcn_raw_buffer_load_b32(
+          uniform_rsrc(r + (a * NW + w) * (kPart / NW)), lane * 128, 0, 0);
+  };
+  touch(src);
+
   for (;;) {
     const int64_t next = row + groups;
     const bool more = next < m;
@@ -1522,7 +1537,10 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
       for (int j = 0; j < 8; ++j) v[k * 8 + j] = x[j];
       __builtin_amdgcn_sched_barrier(0);
     }
+    // the value is of no use, but its register is taken until it arrives
+    if constexpr (TOUCH) asm volatile("" ::"v"(touched));
     src = nsrc;
+    touch(src);
     reg_stage<0>(v);
     reg_stage<1>(v);
     reg_stage<2>(v);
@@ -2084,7 +2102,7 @@ hipError_t launch_large(const uint16_t *in, int64_t in_stride, uint16_t *out, in
 // The parts kernel on m rows.  The workspace holds the deferred parts of an
 // in-place call (2 bytes per element) and then its arrive words (256 bytes per
 // row; together at most the 4 bytes per element of the two passes).
-template <int DT, int A>
+template <int DT, int A, bool TOUCH>
 hipError_t launch_parts(const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride,
                         int64_t m, float scale, float *ws, int spin_limit, hipStream_t stream) {
   const ScaleArgs sc{scale, 1.0f, 0};
@@ -2103,10 +2121,10 @@ hipError_t launch_parts(const uint16_t *in, int64_t in_stride, uint16_t *out, in
                        arrive, m);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, true>), grid, dim3(512), 0, stream, in,
+    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, true, TOUCH>), grid, dim3(512), 0, stream, in,
                        in_stride, out, out_stride, sc, m, (int)groups, defer, arrive, spin_limit);
   } else {
-    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, false>), grid, dim3(512), 0, stream, in,
+    hipLaunchKernelGGL((fwht_parts_kernel<DT, A, false, TOUCH>), grid, dim3(512), 0, stream, in,
                        in_stride, out, out_stride, sc, m, (int)groups, nullptr, nullptr, 0);
   }
   return hipGetLastError();
@@ -2121,16 +2139,16 @@ struct LargeMode {
 };
 
 // Whether m rows run as parts rather than two passes (the bits are the same).
-// Out of place parts win at every m for 2^17 and 2^18 (us, two passes / parts: 1
-// row 11.3 / 8.7 and 12.2 / 10.8; 512 rows of 2^17 139 / 70, 256 rows of 2^18
-// 139 / 95); at 2^19, where each row is read 16 times, with 8 rows (19.3 / 16.8;
-// 6 rows 18.0 / 19.6) up to 2^25 elements (64 rows 74.9 / 58.9; 128 rows, whose
-// reads come from HBM, 141 / 142).  In place the clearing launch and the waits
-// cost 4 us and more: from 8 rows at 2^17 and 2^18 (4 rows of 2^17 12.0 / 13.7, 16
-// rows 15.9 / 12.5; 2 rows of 2^18 12.8 / 18.6, 8 rows 17.0 / 15.1), not at 2^19
-// (33 rows 46 / 54, 64 rows 74.8 / 75.8).
+// Out of place parts win at every m for 2^17 and 2^18 (us, two passes / parts: 16
+// rows 14.3 / 9.4 and 33 rows 24.9 / 18.8; 512 rows of 2^17 126 / 67, 256 rows of
+// 2^18 127 / 83).  At 2^19, where each row is read 16 times, they win from 8 rows
+// (16 rows 23.7 / 19.5, 64 rows 71 / 57, 256 rows 265 / 247) except where the
+// second turn of 32 rows would be nearly empty (33 rows 37.1 / 39.6).  In place
+// the clearing launch and the waits cost 4 us and more: from 8 rows at 2^17 and
+// 2^18 (4 rows of 2^17 12.0 / 13.7, 16 rows 15.6 / 12.3; 2 rows of 2^18 12.8 / 18.6,
+// 33 rows 26.8 / 23.5), not at 2^19 (33 rows 40 / 47, 128 rows 128 / 132).
 bool parts_pay(int L, int64_t m, bool inplace) {
-  if (L == 19) return !inplace && m >= 8 && m <= 64;
+  if (L == 19) return !inplace && m >= 8 && (m <= 32 || m >= 40);
   return !inplace || m >= 8;
 }
 
@@ -2139,9 +2157,14 @@ hipError_t launch_large_size(const uint16_t *in, int64_t in_stride, uint16_t *ou
                              int64_t out_stride, int64_t m, float scale, float *ws, LargeMode mode,
                              hipStream_t stream) {
   if constexpr (LN < 20) {
+    // TOUCH from 96 MiB of input, whose rows come from HBM; rows that come from the
+    // last-level cache lose up to 14% to it
     if (mode.path == kParts || (mode.path == kMeasured && parts_pay(LN, m, in == out)))
-      return launch_parts<DT, 1 << (LN - 15)>(in, in_stride, out, out_stride, m, scale, ws,
-                                              mode.spin_limit, stream);
+      return m << LN >= 3 << 24
+                 ? launch_parts<DT, 1 << (LN - 15), true>(in, in_stride, out, out_stride, m, scale,
+                                                          ws, mode.spin_limit, stream)
+                 : launch_parts<DT, 1 << (LN - 15), false>(in, in_stride, out, out_stride, m, scale,
+                                                           ws, mode.spin_limit, stream);
   }
   return launch_large<DT, 1 << (LN - 15)>(in, in_stride, out, out_stride, m, scale, ws, stream);
 }

@@ -20,9 +20,10 @@ CODE = {"fp16": H.FP16, "bf16": H.BF16}
 
 # (log2 n, rows): one row, groups that are not a multiple of 8, a last turn of
 # groups that is not full, and both sides of the dispatch's lines (in place from
-# 8 rows, 2^19 from 8 rows to 64)
-SHAPES = [(17, 1), (17, 7), (17, 8), (17, 131), (17, 257), (18, 1), (18, 8), (18, 67),
-          (19, 7), (19, 8), (19, 35), (19, 64), (19, 65)]
+# 8 rows, 2^19 from 8 rows but 33 to 39, the next row fetched ahead from 3 * 2^24
+# elements)
+SHAPES = [(17, 1), (17, 7), (17, 8), (17, 131), (17, 257), (17, 384), (18, 1), (18, 8), (18, 67),
+          (18, 193), (19, 7), (19, 8), (19, 32), (19, 33), (19, 40), (19, 96)]
 
 
 def _call(x, out, m, n, dtype, scale, variant, monkeypatch):

@@ -207,7 +207,7 @@ def time_point(d: Device, w, pristine, args, quant: str | None = None) -> tuple[
         alg_bytes = w.m * w.n * 3 + 4 * w.m          # 16-bit read, 1-byte code write, row scales
         outs = codes
     elif w.n > 1 << 16:
-        # two passes through an fp32 workspace (shared: the calls run in stream order)
+        # through a workspace (shared: the calls run in stream order)
         outs = ins if w.inplace else [torch.empty_like(pristine) for _ in range(nbuf)]
         need = H.hadamard_transform_workspace_size(w.m, w.n)
         ws = torch.empty(need, dtype=torch.uint8, device=d.dev)

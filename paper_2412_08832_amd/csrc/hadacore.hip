@@ -1112,12 +1112,14 @@ __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16
     const uint16_t *src = in + next * in_stride;
     const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
 #pragma unroll
-    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
+    for (int k = 0; k < PRE; ++k)
+      raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
   } else if (EPI != kStore16) {
     const uint16_t *src = in + (more ? next : m - 1) * in_stride;
     const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
 #pragma unroll
-    for (int k = 0; k < PRE; ++k) raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
+    for (int k = 0; k < PRE; ++k)
+      raw[k] = loop_load<NT, EPI, CACHED>(src + (w * C + k) * 512, ld_off);
   }
   wave_stages<kMfma, L, C>(v, lane);
   exchange_wave_bits<C, NW, HALVES, TR0>(v, lds);
@@ -1151,7 +1153,8 @@ __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16
       const int W = (k % NW) * C + (k / NW) * NW + w;
       gstore8_u<NT, false>(codes + W * 512, (uint32_t)(lf * 8), qz.codes(&v[k * 8]));
       // the chunks not prefetched yet go out as stored chunks free registers
-      if (k < C - PRE) raw[PRE + k] = loop_load<NT, EPI, CACHED>(src + (w * C + PRE + k) * 512, ld_off);
+      if (k < C - PRE)
+        raw[PRE + k] = loop_load<NT, EPI, CACHED>(src + (w * C + PRE + k) * 512, ld_off);
     }
     if (threadIdx.x == 0) qo.scales[row] = qz.scale;
   }
@@ -1182,8 +1185,9 @@ __global__ __launch_bounds__((1 << L) / (8 * C)) void fwht_block_loop_kernel(
   // With two exchange passes every row takes both slot maps; with one,
   // consecutive rows take them in turn (the loop is unrolled by two).  Either
   // way the LDS needs no barrier before a row's exchange writes.
-  if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false, CACHED>(raw, row, in, in_stride, out, out_stride,
-                                                         sc, qo, m, lds, wave_max, w, lane))
+  if (!loop_row<DT, L, C, HALVES, NT, EPI, PRE, false, CACHED>(raw, row, in, in_stride, out,
+                                                               out_stride, sc, qo, m, lds, wave_max,
+                                                               w, lane))
     return;
   if constexpr (HALVES == 2) {
     do {
@@ -1602,7 +1606,8 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
           const uint16_t *from = defer + (row * A + p) * kPart;
           uint16_t *to = out + row * out_stride + (int64_t)p * kPart;
 #pragma unroll 1
-          for (int i = t; i < kPart / 8; i += 512) gstore_at<false>(to, i * 16u, gload_at<false>(from, i * 16u));
+          for (int i = t; i < kPart / 8; i += 512)
+            gstore_at<false>(to, i * 16u, gload_at<false>(from, i * 16u));
         }
       }
       __syncthreads();  // `seen` is rewritten for the next row
@@ -2460,10 +2465,13 @@ hadacore_status transform_two_pass(const void *in, int64_t in_row_stride, void *
   uint16_t *dst = static_cast<uint16_t *>(out);
   float *ws = static_cast<float *>(workspace);
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const LargeMode mode = large_override();
   const hipError_t err =
       dtype == HADACORE_FP16
-          ? launch_large_dt<HADACORE_FP16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, large_override(), s)
-          : launch_large_dt<HADACORE_BF16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws, large_override(), s);
+          ? launch_large_dt<HADACORE_FP16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws,
+                                           mode, s)
+          : launch_large_dt<HADACORE_BF16>(L, src, in_row_stride, dst, out_row_stride, m, scale, ws,
+                                           mode, s);
   return err == hipSuccess ? HADACORE_SUCCESS : HADACORE_ERROR_LAUNCH;
 }
 

@@ -122,3 +122,38 @@ def test_in_place_calls_on_two_streams(L, m):
         torch.cuda.synchronize()
         for y, r in zip(ys, refs):
             assert torch.equal(y, r)
+
+
+def test_in_place_call_in_a_graph():
+    """The clearing launch and the waits of an in-place call, captured and replayed with
+    eager work between the replays: each replay gives the eager call's bits."""
+    import torch
+    m, n = 40, 1 << 17
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn((m, n), device="cuda", generator=gen).to(torch.bfloat16)
+    y = x.clone()
+    ws = torch.empty(H.hadamard_transform_workspace_size(m, n), dtype=torch.uint8, device="cuda")
+
+    def enqueue(stream):
+        H.hadamard_transform_ws(y.data_ptr(), n, y.data_ptr(), n, m, n, H.BF16, W.default_scale(n),
+                                ws.data_ptr(), ws.numel(), stream)
+
+    enqueue(torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            enqueue(side.cuda_stream)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    for replay in range(4):
+        x.copy_(torch.randn((m, n), device="cuda", generator=gen).to(torch.bfloat16))
+        ref = H.transform(x)
+        y.copy_(x)
+        ws.fill_(0x5C)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, ref), f"replay {replay} differs from eager"

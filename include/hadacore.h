@@ -52,7 +52,8 @@
  * (testing and tuning; read on every call); unset keeps the measured per-size
  * choice.  For 2^16 < n < 2^20 "passes" and "parts" force one of the two ways of
  * hadamard_transform_ws, and "parts-defer" also sets the waits of an in-place
- * call to zero, so that its parts go through the workspace.
+ * call to zero, so that its parts go through the workspace; "parts-wait-N" to at
+ * most N polls.
  *
  * Launches: a call is one kernel launch, or up to two for n > 2^16; m so
  * large that a launch would exceed 2^31 work-items (2^33 elements) is split

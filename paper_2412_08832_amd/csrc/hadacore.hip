@@ -1436,7 +1436,9 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 // resident together: when it runs out, the workgroup leaves its part in `defer`
 // and sets its bit in the same word.  Whoever moves the word second completes
 // the part: the bit's setter if it finds the count at A, else the workgroup
-// that makes the count A, which copies the parts whose bits it finds.  Arrive
+// that makes the count A, which copies the parts whose bits it finds.  A
+// workgroup whose wait ran out has a partner that is not running and waits for no
+// further row of the launch, so it loses one limit in all, not one per row.  Arrive
 // words are 256 bytes apart: as neighbours, their atomics cost 5-15% more.
 constexpr int kPartL = 15;
 constexpr int kArriveBits = 8;    // arrive word: count in bits 0-7, deferred parts above
@@ -1492,11 +1494,13 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
   static_assert(A <= 32 - kArriveBits && A >= 2, "one bit of the arrive word per part");
   __shared__ float4 lds[kPart / 4 / 2];
   __shared__ uint32_t seen;  // INPLACE: what thread 0 tells the others of the arrive word
+  __shared__ int polls;      // INPLACE, thread 0: polls allowed for a row (LDS spares a register)
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
   const PartsSlot slot = parts_slot<A>((int)blockIdx.x, groups);
   const int a = slot.a;
   int64_t row = slot.group;
   if (row >= m) return;
+  if (INPLACE && threadIdx.x == 0) polls = spin_limit;
 
   const int lane = threadIdx.x & (kWave - 1);
   const float s1 = (a & 1) != 0 ? -sc.scale : sc.scale;
@@ -1564,10 +1568,11 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
     if constexpr (INPLACE) {
       if (threadIdx.x == 0) {
         uint32_t now = before + 1;
-        for (int i = 0; (now & kCount) != A && i < spin_limit; ++i) {
+        for (int i = polls; (now & kCount) != A && i > 0; --i) {
           __builtin_amdgcn_s_sleep(1);
           now = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if ((now & kCount) != A) polls = 0;
         const uint32_t owed = (before & kCount) == A - 1 ? before >> kArriveBits : 0u;
         seen = (now & kCount) | (owed << kArriveBits);
       }
@@ -2249,16 +2254,23 @@ int front_override() {
 }
 
 // The same variable for n > 2^16: "passes" and "parts" force a path, "parts-defer"
-// the parts with no wait, so that in-place parts go through the workspace.
-// Otherwise the wait is 4096 polls, a few milliseconds, far beyond any row's time.
+// the parts with no wait, so that in-place parts go through the workspace, and
+// "parts-wait-N" the parts with waits of at most N polls.  Otherwise a wait is at
+// most kSpinLimit polls, a few milliseconds, far beyond any row's time.
+constexpr int kSpinLimit = 4096;
+
 LargeMode large_override() {
   const char *v = getenv("HADACORE_VARIANT");
   if (v != nullptr) {
     if (strcmp(v, "passes") == 0) return {kTwoPasses, 0};
-    if (strcmp(v, "parts") == 0) return {kParts, 4096};
+    if (strcmp(v, "parts") == 0) return {kParts, kSpinLimit};
     if (strcmp(v, "parts-defer") == 0) return {kParts, 0};
+    if (strncmp(v, "parts-wait-", 11) == 0) {
+      const long polls = strtol(v + 11, nullptr, 10);
+      return {kParts, polls < 0 ? 0 : polls > kSpinLimit ? kSpinLimit : (int)polls};
+    }
   }
-  return {kMeasured, 4096};
+  return {kMeasured, kSpinLimit};
 }
 
 // Architecture check, cached per device: 0 unknown, 1 gfx950, 2 other.

@@ -80,6 +80,44 @@ def test_parts_match_oracle_and_two_passes(oracle, monkeypatch, L, m, dtype):
         assert torch.equal(_bits(y)[:, n:], _bits(x)[:, n:]), "in place wrote past a row"
 
 
+@pytest.mark.parametrize("polls", [1, 4, 16])
+@pytest.mark.parametrize("L,m", [(17, 1031), (18, 517), (19, 259)])
+def test_a_wait_that_ran_out_is_the_last_of_its_workgroup(monkeypatch, L, m, polls):
+    """In place with short waits, so that stored and deferred parts mix in one call: the
+    bits of the two passes, and a workgroup whose wait ran out waits for no later row.
+
+    The arrive words that the call leaves in the workspace show it: a part's bit is set
+    where its workgroup stored it in the workspace.  A workgroup that no longer waits
+    stores a part itself only where it is the last of its row to arrive, so of the
+    workgroups that ran out on earlier rows at most one a row has no bit.
+    """
+    import torch
+    n, A = 1 << L, 1 << (L - 15)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    x = torch.randn((m, n), device="cuda", generator=gen, dtype=torch.bfloat16)
+    monkeypatch.setenv("HADACORE_VARIANT", "passes")
+    want = H.transform(x)
+    monkeypatch.setenv("HADACORE_VARIANT", f"parts-wait-{polls}")
+    ws = torch.full((H.hadamard_transform_workspace_size(m, n),), 0x5C, dtype=torch.uint8,
+                    device="cuda")
+    y = x.clone()
+    H.transform(y, out=y, workspace=ws)
+    assert torch.equal(_bits(y), _bits(want))
+    # deferred parts (2 bytes an element), then a row's arrive word every 256 bytes
+    words = ws.view(torch.int32)[m * n // 2:].view(-1, 64)[:m, 0].cpu().numpy()
+    assert ((words & 0xFF) == A).all()
+    deferred = (words[:, None] >> (8 + np.arange(A))) & 1
+    say(f"  n=2^{L} m={m} polls={polls}: {deferred.mean():.3f} of the parts deferred")
+    slots = 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    groups = slots // A
+    assert m > 4 * groups, "several rows a group"
+    ran_out = np.zeros((groups, A), bool)
+    for r in range(m):
+        waits = ran_out[r % groups] & (deferred[r] == 0)
+        assert waits.sum() <= 1, f"row {r}: parts {np.flatnonzero(waits)} waited again"
+        ran_out[r % groups] |= deferred[r] != 0
+
+
 def test_parts_special_values(monkeypatch):
     """Infinities, NaN, overflow and an all-zero row: parts and two passes, same bits."""
     import torch

@@ -1344,13 +1344,10 @@ __global__ __launch_bounds__(256) void fwht_row_kernel(const uint16_t *in, int64
 // the 8 columns of one lane l of one tile (16-byte load, two 16-byte stores);
 // CW = 4 (A >= 16, to keep A*CW <= 128 values): the 4 columns of one half
 // (8-byte load, one 16-byte store), waves ordered by (tile, half).
-// Loads and workspace stores take the ordinary cache policy, the second pass
-// streams: of seven combinations the fastest at every size tried (us, against
-// streaming everywhere with SC1 workspace stores: 33 rows of 2^20 82.5 -> 74.9, 8
-// rows 30.0 -> 25.2, 128 rows 278 -> 267; 33 rows of 2^19 in place 46.3 -> 40.5).
-// The workspace is then written through the L2 and, up to its 256 MiB, read back
-// from the last-level cache.
-template <int DT, int A, int CW>
+// STREAM: nontemporal loads and workspace stores (see column_streams); otherwise
+// both take the ordinary cache policy, so that the workspace is written through the
+// L2 and, up to the 256 MiB of the last-level cache, read back from there.
+template <int DT, int A, int CW, bool STREAM>
 __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, int64_t in_stride,
                                                           float *ws, int64_t m, float scale) {
   static_assert(CW == 8 || CW == 4, "8 or 4 columns per thread");
@@ -1371,7 +1368,7 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 #pragma unroll
   for (int t = 0; t < A; ++t) {
     const T16 *ptr = reinterpret_cast<const T16 *>(src + (int64_t)t * kBlock);
-    const T16 r = *ptr;
+    const T16 r = STREAM ? __builtin_nontemporal_load(ptr) : *ptr;
     uint32_t h[CW];
     unpack16<CW>(r, h);
 #pragma unroll
@@ -1400,8 +1397,8 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 #pragma unroll
     for (int hh = 0; hh < CW / 4; ++hh) {
       const f4 x = {v[t][4 * hh], v[t][4 * hh + 1], v[t][4 * hh + 2], v[t][4 * hh + 3]};
-      gstore_at<false>(wdst + (int64_t)t * kBlock, (uint32_t)(l * 16 + hh * 1024),
-                       __builtin_bit_cast(u4, x));
+      gstore_at<STREAM>(wdst + (int64_t)t * kBlock, (uint32_t)(l * 16 + hh * 1024),
+                        __builtin_bit_cast(u4, x));
     }
   }
 }
@@ -2085,6 +2082,23 @@ hipError_t launch_dt_one(int L, const uint16_t *in, int64_t in_stride, uint16_t 
   }
 }
 
+// Whether the column pass streams: for `e` elements above 2^21 up to 2^23, in place
+// up to 2^22, where the workspace (8 to 32 MiB) about fills the L2s and its dirty
+// lines are written back as the second pass starts.  us in four states of the
+// caches (rot: three buffer sets in turn; prod: the input written by a copy before,
+// both timed; pipe: a copy of the output after as well; cold: the last-level cache
+// full of other data), ordinary / streaming:
+//  - 4 rows of 2^20 18.6 / 16.8, 22.2 / 20.5, 26.0 / 24.2, 22.0 / 20.6; in place 22.1 /
+//    20.6, 24.0 / 22.3, 27.7 / 26.4, 23.6 / 22.3
+//  - 8 rows 24.6 / 22.9, 28.2 / 27.6, 35.8 / 35.8, 27.6 / 26.6; in place 25.6 / 25.5,
+//    28.3 / 29.8, 36.0 / 38.2, 27.8 / 28.7
+//  - 2 rows 16.2 / 16.3, 20.0 / 20.2, 21.8 / 21.6, 18.6 / 19.4
+//  - 33 rows 73.9 / 82.4, 92.8 / 102, 120 / 128, 82.7 / 88.8
+//  - 128 rows 262 / 279, 366 / 370, 466 / 471, 280 / 281
+bool column_streams(int64_t e, bool inplace) {
+  return e > 1 << 21 && e <= (inplace ? 1 << 22 : 1 << 23);
+}
+
 // n = A * 2^15, A = 4..32: the column pass into the fp32 workspace, then the
 // n = 2^15 block kernel on the workspace rows (fp32 input, VALU front), each
 // writing block t of its output row.
@@ -2095,8 +2109,12 @@ hipError_t launch_large(const uint16_t *in, int64_t in_stride, uint16_t *out, in
   constexpr int kBlock = 1 << 15;
   const int64_t threads = m * (kBlock / CW);
   const dim3 grid((uint32_t)((threads + 255) / 256));
-  hipLaunchKernelGGL((fwht_column_kernel<DT, A, CW>), grid, dim3(256), 0, stream, in, in_stride, ws,
-                     m, scale);
+  if (column_streams(m * A * kBlock, in == out))
+    hipLaunchKernelGGL((fwht_column_kernel<DT, A, CW, true>), grid, dim3(256), 0, stream, in,
+                       in_stride, ws, m, scale);
+  else
+    hipLaunchKernelGGL((fwht_column_kernel<DT, A, CW, false>), grid, dim3(256), 0, stream, in,
+                       in_stride, ws, m, scale);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   constexpr Cfg c = config<15, kStore16, kValu>();

@@ -34,3 +34,22 @@ def test_rows_do_not_depend_on_the_size_of_the_call(n, total, more, pad):
     z = buf.clone()
     H.transform(z[:, :n], out=z[:, :n])
     assert torch.equal(z[:, :n], y) and torch.equal(z[:, n:], buf[:, n:])
+
+
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
+@pytest.mark.parametrize("L,m", [(18, 9), (19, 4), (19, 5), (19, 8), (19, 9), (19, 16), (19, 17),
+                                 (20, 2), (20, 3), (20, 5), (20, 8), (20, 9)])
+def test_two_pass_rows_do_not_depend_on_the_size_of_the_call(monkeypatch, L, m, dtype):
+    """The column pass streams for calls of 2^21 to 2^23 elements (2^22 in place): the
+    bits of the same rows one at a time, below that range."""
+    import torch
+    monkeypatch.setenv("HADACORE_VARIANT", "passes")
+    n = 1 << L
+    gen = torch.Generator(device="cuda").manual_seed(L * 100 + m)
+    x = torch.randn((m, n + 8), device="cuda", generator=gen)
+    x = x.to({"fp16": torch.float16, "bf16": torch.bfloat16}[dtype])
+    ref = torch.cat([H.transform(x[r : r + 1, :n]) for r in range(m)])
+    assert torch.equal(H.transform(x[:, :n]), ref)
+    z = x.clone()
+    H.transform(z[:, :n], out=z[:, :n])
+    assert torch.equal(z[:, :n], ref) and torch.equal(z[:, n:], x[:, n:])

@@ -1423,8 +1423,8 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 //
 // TOUCH: while a row is in its stages, its workgroups fetch the lines of their
 // next row into the L2, one 4-byte load per line, a share each (us, without /
-// with: 512 rows of 2^17 70 / 67, 256 rows of 2^18 93 / 83, 128 rows of 2^19 142 /
-// 123).
+// with: 512 rows of 2^17 71 / 68, 256 rows of 2^18 95 / 85, 128 rows of 2^19 144 /
+// 125; rows that come from the last-level cache lose up to 14%, see parts_touch).
 //
 // In place (INPLACE), no part may be stored before all A workgroups have read
 // the row.  Each workgroup counts itself in the row's arrive word once its
@@ -2127,22 +2127,27 @@ hipError_t launch_large(const uint16_t *in, int64_t in_stride, uint16_t *out, in
   return hipGetLastError();
 }
 
+// Groups of A workgroups that the chip holds at once, two workgroups per CU.
+int64_t parts_groups(int A) {
+  const int64_t slots = (int64_t)device_cus() * 2;
+  return slots / A > 0 ? slots / A : 1;
+}
+
 // The parts kernel on m rows.  The workspace holds the deferred parts of an
 // in-place call (2 bytes per element) and then its arrive words (256 bytes per
 // row; together at most the 4 bytes per element of the two passes).
-template <int DT, int A, bool TOUCH>
+template <int DT, int A, bool INPLACE, bool TOUCH>
 hipError_t launch_parts(const uint16_t *in, int64_t in_stride, uint16_t *out, int64_t out_stride,
                         int64_t m, float scale, float *ws, int spin_limit, hipStream_t stream) {
   const ScaleArgs sc{scale, 1.0f, 0};
   // groups of A workgroups that fit the chip at once, a multiple of 8 where
   // there are more (see parts_slot); groups past row m end at once
-  const int64_t slots = (int64_t)device_cus() * 2;
-  const int64_t most = slots / A > 0 ? slots / A : 1;
+  const int64_t most = parts_groups(A);
   int64_t groups = m;
   if (groups > 8) groups = (groups + 7) & ~int64_t(7);
   if (groups > most) groups = most;
   const dim3 grid((uint32_t)(groups * A));
-  if (in == out) {
+  if constexpr (INPLACE) {
     uint16_t *defer = reinterpret_cast<uint16_t *>(ws);
     uint32_t *arrive = reinterpret_cast<uint32_t *>(defer + m * (int64_t(A) << kPartL));
     hipLaunchKernelGGL(clear_arrive_kernel, dim3((uint32_t)((m + 255) / 256)), dim3(256), 0, stream,
@@ -2166,35 +2171,71 @@ struct LargeMode {
   int spin_limit;
 };
 
-// Whether m rows run as parts rather than two passes (the bits are the same).
-// Out of place parts win at every m for 2^17 and 2^18 (us, two passes / parts: 16
-// rows 14.3 / 9.4 and 33 rows 24.9 / 18.8; 512 rows of 2^17 126 / 67, 256 rows of
-// 2^18 127 / 83).  At 2^19, where each row is read 16 times, they win from 8 rows
-// (16 rows 23.7 / 19.5, 64 rows 71 / 57, 256 rows 265 / 247) except where the
-// second turn of 32 rows would be nearly empty (33 rows 37.1 / 39.6).  In place
-// the clearing launch and the waits cost 4 us and more: from 8 rows at 2^17 and
-// 2^18 (4 rows of 2^17 12.0 / 13.7, 16 rows 15.6 / 12.3; 2 rows of 2^18 12.8 / 18.6,
-// 33 rows 26.8 / 23.5), not at 2^19 (33 rows 40 / 47, 128 rows 128 / 132).
+// Whether m rows run as parts rather than two passes (the bits are the same), and
+// whether the parts fetch ahead (TOUCH).  us in the four states of the caches named
+// at column_streams; each line is drawn so that no state loses much.
+//  - 2^17 out of place: parts at every m (1 row 8.9 / 11.4 / 13.4 / 13.5 against 10.1
+//    / 11.7 / 13.7 / 14.2), fetching ahead from 96 MiB, 384 rows (768 rows 93 / 168 /
+//    243 / 105 with, 102 / 174 / 248 / 113 without).
+//  - 2^18 out of place: from 8 rows.  Fewer than 8 groups lie across the XCDs, and
+//    each XCD fetches the whole row (2 rows 10.8 / 15.1 / 17.4 / 18.0 against 11.3 /
+//    13.3 / 15.6 / 14.6).  Up to a quarter of the groups, 16 rows, half the CUs are
+//    idle and nothing overlaps the reads, so that fetching a row as the first thing
+//    helps where it comes from HBM (12 rows 11.9 / 17.6 / 19.3 / 16.4 with, 11.9 / 18.0
+//    / 19.4 / 19.1 without).  Beyond, fetching ahead only from 96 MiB, 192 rows (64.6 /
+//    103 / 135 / 74 with, 71 / 106 / 133 / 80 without; 64 rows 23.0 / 33.0 / 46.0 / 29.5
+//    with, 21.8 / 31.8 / 44.7 / 31.2 without).
+//  - 2^19 out of place, each row read 16 times: from one and a half turns of the
+//    groups, 48 rows, always fetching ahead (48 rows 48.5 / 62.8 / 81.9 / 56.8 against
+//    51.2 / 66.1 / 85.7 / 61.2, and 44.1 / 59.0 / 77.7 / 62.8 without fetching; 65 rows
+//    70 / 90 / 121 / 81 against 73 / 92 / 117 / 78, and 66 / 86 / 116 / 95; 96 rows 94 /
+//    134 / 164 / 105 against 98 / 139 / 177 / 107, and 110 / 138 / 159 / 122).  Below,
+//    parts gain on warm buffers at some sizes and lose more cold (16 rows 20.2 / 26.4 /
+//    34.0 / 29.1 against 24.7 / 26.9 / 35.1 / 25.4; 40 rows 40.7 / 53.2 / 69.4 / 61.5
+//    against 43.5 / 55.6 / 71.6 / 53.4), or lose everywhere (8 rows 16.4 / 23.6 / 25.6 /
+//    27.0 against 18.6 / 18.4 / 22.8 / 18.7; 17 rows 28.2 / 34.8 / 42.8 / 42.4 against
+//    26.3 / 31.5 / 39.0 / 31.3).
+//  - In place the clearing launch and the waits cost 4 us and more.  2^17 from 12 rows
+//    (12.3 / 15.9 / 18.6 / 19.8 against 14.2 / 16.4 / 19.5 / 16.2; 8 rows 12.0 / 15.2 / 17.3
+//    / 19.7 against 12.8 / 14.6 / 17.0 / 15.6), never fetching ahead (768 rows 110 / 183 /
+//    260 / 121 with, 111 / 179 / 264 / 116 without).  2^18 from 16 rows (15.4 / 21.5 /
+//    23.2 / 25.0 against 19.9 / 22.3 / 26.1 / 21.6; 9 rows 14.4 / 19.2 / 21.9 / 23.5
+//    against 17.8 / 19.3 / 22.2 / 17.4), fetching ahead from 192.  2^19 never (32 rows
+//    37.4 / 46.2 / 61.3 / 52.3 against 35.6 / 43.7 / 56.8 / 44.0, 128 rows 134 / 186 / 224
+//    / 145 against 128 / 181 / 231 / 141).
 bool parts_pay(int L, int64_t m, bool inplace) {
-  if (L == 19) return !inplace && m >= 8 && (m <= 32 || m >= 40);
-  return !inplace || m >= 8;
+  if (inplace) return L == 17 ? m >= 12 : L == 18 && m >= 16;
+  return L == 17 || (L == 18 ? m >= 8 : 2 * m >= 3 * parts_groups(16));
+}
+
+bool parts_touch(int L, int64_t m, bool inplace) {
+  if (L == 19) return true;
+  if (L == 18 && !inplace && 4 * m <= parts_groups(8)) return true;
+  return !(L == 17 && inplace) && m << L >= 3 << 24;
 }
 
 template <int DT, int LN>
 hipError_t launch_large_size(const uint16_t *in, int64_t in_stride, uint16_t *out,
                              int64_t out_stride, int64_t m, float scale, float *ws, LargeMode mode,
                              hipStream_t stream) {
+  constexpr int A = 1 << (LN - 15);
   if constexpr (LN < 20) {
-    // TOUCH from 96 MiB of input, whose rows come from HBM; rows that come from the
-    // last-level cache lose up to 14% to it
-    if (mode.path == kParts || (mode.path == kMeasured && parts_pay(LN, m, in == out)))
-      return m << LN >= 3 << 24
-                 ? launch_parts<DT, 1 << (LN - 15), true>(in, in_stride, out, out_stride, m, scale,
-                                                          ws, mode.spin_limit, stream)
-                 : launch_parts<DT, 1 << (LN - 15), false>(in, in_stride, out, out_stride, m, scale,
-                                                           ws, mode.spin_limit, stream);
+    const bool inplace = in == out;
+    if (mode.path == kParts || (mode.path == kMeasured && parts_pay(LN, m, inplace))) {
+      const auto parts = [&](auto with_inplace, auto with_touch) {
+        return launch_parts<DT, A, decltype(with_inplace)::value, decltype(with_touch)::value>(
+            in, in_stride, out, out_stride, m, scale, ws, mode.spin_limit, stream);
+      };
+      // parts_touch never holds for LN = 17 in place and always does for LN = 19
+      constexpr std::bool_constant<LN == 19> always{};
+      const bool touch = parts_touch(LN, m, inplace);
+      if (inplace)
+        return touch ? parts(std::true_type{}, std::bool_constant<LN != 17>{})
+                     : parts(std::true_type{}, always);
+      return touch ? parts(std::false_type{}, std::true_type{}) : parts(std::false_type{}, always);
+    }
   }
-  return launch_large<DT, 1 << (LN - 15)>(in, in_stride, out, out_stride, m, scale, ws, stream);
+  return launch_large<DT, A>(in, in_stride, out, out_stride, m, scale, ws, stream);
 }
 
 template <int DT>

@@ -19,9 +19,8 @@ pytestmark = pytest.mark.gpu
 CODE = {"fp16": H.FP16, "bf16": H.BF16}
 
 # (log2 n, rows): one row, groups that are not a multiple of 8, a last turn of
-# groups that is not full, and both sides of the dispatch's lines (in place from
-# 8 rows, 2^19 from 8 rows but 33 to 39, the next row fetched ahead from 3 * 2^24
-# elements)
+# groups that is not full, and both sides of lines of the dispatch (the others are
+# in test_path_by_size)
 SHAPES = [(17, 1), (17, 7), (17, 8), (17, 131), (17, 257), (17, 384), (18, 1), (18, 8), (18, 67),
           (18, 193), (19, 7), (19, 8), (19, 32), (19, 33), (19, 40), (19, 96)]
 
@@ -78,6 +77,30 @@ def test_parts_match_oracle_and_two_passes(oracle, monkeypatch, L, m, dtype):
         _call(y, y, m, n, dtype, scale, variant, monkeypatch)
         assert torch.equal(_bits(y)[:, :n], _bits(out)[:, :n]), f"in place differs ({variant})"
         assert torch.equal(_bits(y)[:, n:], _bits(x)[:, n:]), "in place wrote past a row"
+
+
+@pytest.mark.parametrize("L,m,inplace,parts", [
+    (17, 1, False, True), (18, 7, False, False), (18, 8, False, True), (18, 16, False, True),
+    (18, 17, False, True), (18, 192, False, True), (19, 16, False, False), (19, 17, False, False),
+    (19, 40, False, False), (19, 47, False, False), (19, 48, False, True), (19, 65, False, True),
+    (17, 11, True, False), (17, 12, True, True), (17, 384, True, True), (18, 15, True, False),
+    (18, 16, True, True), (18, 192, True, True), (19, 96, True, False)])
+def test_path_by_size(monkeypatch, L, m, inplace, parts):
+    """Both sides of each line of the dispatch: which way a call takes, seen from the
+    workspace (the two passes fill it; the parts leave its end alone), and the bits of
+    the other way."""
+    import torch
+    monkeypatch.delenv("HADACORE_VARIANT", raising=False)
+    n = 1 << L
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    x = torch.randn((m, n), device="cuda", generator=gen).to(torch.bfloat16)
+    ws = torch.full((H.hadamard_transform_workspace_size(m, n),), 0x5C, dtype=torch.uint8,
+                    device="cuda")
+    y = x.clone() if inplace else torch.empty_like(x)
+    H.transform(y if inplace else x, out=y, workspace=ws)
+    assert bool((ws[-4096:] == 0x5C).all()) == parts
+    monkeypatch.setenv("HADACORE_VARIANT", "passes" if parts else "parts")
+    assert torch.equal(_bits(y), _bits(H.transform(x)))
 
 
 @pytest.mark.parametrize("polls", [1, 4, 16])

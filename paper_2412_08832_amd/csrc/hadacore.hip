@@ -1813,12 +1813,15 @@ bool whole_lines(const void *p, int64_t pitch_bytes, int64_t row_bytes) {
   return pitch_bytes == row_bytes || (pitch_bytes % 128 == 0 && row_bytes % 128 == 0);
 }
 
-// Cache policy of a call by its size, as measured in us against streaming loads
-// and, on whole lines, SC1 stores (which it is for all sizes not named here).
+// Cache policy of a call by its size, as measured against streaming loads and, on
+// whole lines, SC1 stores (which it is for all sizes not named here), in four
+// states of the caches: rot, three buffer sets in turn; prod, the input written by a
+// copy before, both timed; pipe, a copy of the output after as well; cold, the 256
+// MiB last-level cache full of other, modified data.
 //
 // `cached`: input loads with the ordinary cache policy, so that an input that is
-// in the 256 MiB last-level cache, put there by its producer or an earlier
-// reader, is served from it and stays.
+// in the last-level cache, put there by its producer or an earlier reader, is
+// served from it and stays.
 // `sc1`: output stores with the SC1 bit (see gstore_u), on whole lines only.
 struct CallPolicy {
   bool cached;
@@ -1843,34 +1846,31 @@ bool cached_out_of_place(int epi, int L, int64_t e) {
 }
 
 // In place, 16-bit output.  Cached loads bring the lines into the L2 that the
-// stores then write; SC1 stores do not go with them (1-5% slower than either
-// alone).
-//  - Up to 2^22 elements (2^23 at n = 1024 and 4096) stores without SC1 gain 5-18%:
-//    n = 128 2^16 elements 2.42 -> 2.13, n = 4096 2^21 3.88 -> 3.67, n = 1024 2^23 7.6
-//    -> 6.9.
-//  - Rows on whole lines, cached loads and no SC1: n = 1024 +6 to +12% from 1.5 *
-//    2^22 to 2^25, n = 4096 and 8192 +1 to +8% above 2^23, n = 16384 +5 to +8% above
-//    2^24, n = 32768 +5 to +10% from 2^24; other n lose or are equal.
+// stores then write; SC1 stores do not go with them.  Gains of the ordinary policy
+// in percent, in the four states rot / prod / pipe / cold:
+//  - Rows on whole lines, above 2^24 elements (32 MiB, the L2s together) up to 2^25:
+//    n = 1024 +7 / -3 / +6 / -1 to -5, 4096 +7 / -3 / +5 / -3 to -7, 8192 +5 / -3 / +5 /
+//    -6 to -9, 16384 +6 to +10 / -4 / +5 / 0.  Other n gain in pipe only (n <= 512 0 / -4 /
+//    +5 / -5, 2048 -4 / -4 / +4 to +6 / -6 to -9, 32768 +5 to +9 / -3 / -3 to +3 / -11), and
+//    so do smaller calls (n = 4096, 2^24 +1 / -5 / +5 / -13).
+//  - Small calls without SC1 and with streaming loads gain in rot only, where the
+//    output of a call is the next one's input (n = 128: 2^16 elements +12 / -7 / -4 /
+//    -4, 2^20 +8 / -14 / -12 / -5, 2^22 +6 / -29 / -4 / -5), so they keep SC1.
 //  - Rows off the lines with less than a line between them, so that neighbours
-//    share lines: n <= 128 +4 to +56% from 2^23 (n = 32, 2^25 elements 42.4 ->
-//    29.5), n = 256-1024 +3 to +16% up to 2^25 (2^26 -13 to +4%), n = 4096 and 8192
-//    +0 to +9% above 2^23 up to 2^25 (2^26 -2 to -4%), n = 16384 +4 to +9% above
-//    2^24, n = 32768 +6 to +13% from 2^24; n = 2048 is equal, and rows further
-//    apart lose up to 17%.
+//    share lines: n <= 128 from 2^23 (n = 32, 2^25 +34 / +16 / +12 / +41), n = 256-1024
+//    up to 2^25 (n = 256, 2^24 +8 / +11 / +9 / +5; above, prod -2 to -11), n = 4096 and
+//    8192 above 2^23 up to 2^25 (0 to +9 / +1 to +6 / +4 to +6 / -10 to 0), n = 16384 and
+//    32768 above 2^24 up to 2^25 (+3 to +10 / +1 to +5 / 0 to +3 / -16 to +1); n = 2048
+//    loses, and so do rows further apart (up to 17%).
 CallPolicy in_place_policy(int L, int64_t e, bool whole, int64_t gap_bytes) {
-  const int64_t small = L == 10 || L == 12 ? 1 << 23 : 1 << 22;
-  if (e <= small) return {false, false};
-  const bool upto25 = e <= 1 << 25;
+  const bool upto25 = e <= 1 << 25, mid = e > 1 << 24 && upto25;
   bool cached = false;
-  if (L == 15)
-    cached = e >= 1 << 24;
-  else if (L == 14)
-    cached = e > 1 << 24 && upto25;
-  else if (L == 12 || L == 13 || (L == 10 && whole))
-    cached = e > 1 << 23 && upto25;
-  else if (L <= 10 && !whole)
+  if (whole)
+    cached = mid && (L == 10 || (L >= 12 && L <= 14));
+  else if (gap_bytes < 128 && L <= 9)
     cached = e >= 1 << 23 && (L <= 7 || upto25);
-  if (!whole && gap_bytes >= 128) cached = false;
+  else if (gap_bytes < 128 && L != 11)
+    cached = L <= 13 ? e > 1 << 23 && upto25 : mid;
   return {cached, whole && !cached};
 }
 
@@ -2084,10 +2084,8 @@ hipError_t launch_dt_one(int L, const uint16_t *in, int64_t in_stride, uint16_t 
 
 // Whether the column pass streams: for `e` elements above 2^21 up to 2^23, in place
 // up to 2^22, where the workspace (8 to 32 MiB) about fills the L2s and its dirty
-// lines are written back as the second pass starts.  us in four states of the
-// caches (rot: three buffer sets in turn; prod: the input written by a copy before,
-// both timed; pipe: a copy of the output after as well; cold: the last-level cache
-// full of other data), ordinary / streaming:
+// lines are written back as the second pass starts.  us in the four states of the
+// caches named at CallPolicy (rot, prod, pipe, cold), ordinary / streaming:
 //  - 4 rows of 2^20 18.6 / 16.8, 22.2 / 20.5, 26.0 / 24.2, 22.0 / 20.6; in place 22.1 /
 //    20.6, 24.0 / 22.3, 27.7 / 26.4, 23.6 / 22.3
 //  - 8 rows 24.6 / 22.9, 28.2 / 27.6, 35.8 / 35.8, 27.6 / 26.6; in place 25.6 / 25.5,
@@ -2173,7 +2171,7 @@ struct LargeMode {
 
 // Whether m rows run as parts rather than two passes (the bits are the same), and
 // whether the parts fetch ahead (TOUCH).  us in the four states of the caches named
-// at column_streams; each line is drawn so that no state loses much.
+// at CallPolicy; each line is drawn so that no state loses much.
 //  - 2^17 out of place: parts at every m (1 row 8.9 / 11.4 / 13.4 / 13.5 against 10.1
 //    / 11.7 / 13.7 / 14.2), fetching ahead from 96 MiB, 384 rows (768 rows 93 / 168 /
 //    243 / 105 with, 102 / 174 / 248 / 113 without).

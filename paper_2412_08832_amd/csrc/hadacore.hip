@@ -1828,19 +1828,23 @@ struct CallPolicy {
   bool sc1;
 };
 
-// Out of place (n = 64-16384): on three rotating buffer sets cached loads gain 10
-// to 20% at 2^24 and 2^25 elements; with input written by the kernel before, both
-// kernels together, 4 to 7% up to 2^25, 1% at 1.5 * 2^25, -4% at 2^26; with input
-// in neither cache they lose 2 to 5%.  From 2^26 (128 MiB) all three lose, and
-// below 2^23 they are equal.  The lower ends differ: 2^23 gains 8-10% up to n =
-// 1024 and loses 4% above; n = 32768 gains 16% at 2^25, 0 at 2^24; quantized
-// output gains 3-11% from 2^23 (n <= 128), 4-8% above it (n <= 1024) and 11-13% at
-// 2^25 above (2^24 -3%).  Quantized n = 65536 gains 6-21% from 2^22: its ending
-// workgroups all read the last row once more.
+// Out of place.  Gains of ordinary loads in percent, in the four states rot / prod /
+// pipe / cold; cold is 0 to -4 with a cache full of unmodified data, and a reader of
+// the input after the call, timed along, gains 7 to 13.
+//  - 16 bits, up to 3 * 2^23 elements: +2 to +20 / -2 to +1 / -2 to 0 / -5 to -19.  Above,
+//    where input, output and what reads it no longer fit the cache together, pipe
+//    loses 3 to 6 at 2^24.75 and 8 at 2^25, against +10 to +16 in rot: they stream.
+//    The lower ends differ: 2^23 gains 9-14 in rot up to n = 1024, and above it loses
+//    1-9 in rot and 4-5 in prod; n = 32768 loses 4 in rot up to 2^24.
+//  - Quantized, up to 2^25: +1 to +18 / -5 to +1 / -3 to 0 / -9 to -23, from 2^23 (n <=
+//    128), above it (n <= 1024) or above 2^24 (more; below, -1 to -8 in rot).  From
+//    2^25.5 prod loses 16 to 22.
+//  - Quantized n = 65536, from 2^22: +4 to +19 / +9 to +19 / +6 to +15 / -5 to +7: its
+//    ending workgroups all read the last row once more.
 bool cached_out_of_place(int epi, int L, int64_t e) {
-  if (e > 1 << 25) return false;
   if (epi == kStore16)
-    return L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24;
+    return e <= 3 << 23 && (L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24);
+  if (e > 1 << 25) return false;
   if (L == 16) return e >= 1 << 22;
   return L <= 7 ? e >= 1 << 23 : L <= 10 ? e > 1 << 23 : e > 1 << 24;
 }

@@ -1,6 +1,7 @@
 """Calls whose size picks another cache policy for their loads or stores give
-the bits of the same rows in a call of another size, on both sides of each line
-of the rule, with aligned rows and with rows off the 128-byte lines."""
+the bits of the same rows in a call of another size, for every n that has several
+policies, on both sides of each line of the rules, with aligned rows, rows that
+share 128-byte lines and rows further apart, in both dtypes."""
 from __future__ import annotations
 
 import pytest
@@ -9,20 +10,23 @@ from paper_2412_08832_amd import hadacore as H
 
 pytestmark = pytest.mark.gpu
 
-# (n, total elements): the lines of the rules lie at 2^22 .. 2^25, other ones for each
-# size, for quantized output, and in place by whether rows share lines (pad 8) or not
-SIZES = [(64, 1 << 23), (128, 1 << 22), (1024, 1 << 24), (4096, 1 << 22), (4096, 1 << 24),
-         (16384, 1 << 25), (32768, 1 << 25), (65536, 1 << 22), (65536, 1 << 25)]
+# (n, total elements): every n that has ordinary loads, at each count of elements where
+# some rule (16 bits out of place, quantized, in place with whole lines or rows that
+# share lines) changes, one row fewer and one more
+SIZES = [(1 << L, total) for L in range(4, 17)
+         for total in (1 << 23, 1 << 24, 3 << 23, 1 << 25)] + [(65536, 1 << 22)]
 
 
+@pytest.mark.parametrize("dtype", ["fp16", "bf16"])
 @pytest.mark.parametrize("pad", [0, 8, 72])
-@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("more", [-1, 0, 1])
 @pytest.mark.parametrize("n,total", SIZES)
-def test_rows_do_not_depend_on_the_size_of_the_call(n, total, more, pad):
+def test_rows_do_not_depend_on_the_size_of_the_call(n, total, more, pad, dtype):
     import torch
     m = total // n + more
     gen = torch.Generator(device="cuda").manual_seed(n)
-    buf = torch.randn((m, n + pad), device="cuda", generator=gen).to(torch.bfloat16)
+    buf = torch.randn((m, n + pad), device="cuda", generator=gen)
+    buf = buf.to({"fp16": torch.float16, "bf16": torch.bfloat16}[dtype])
     x = buf[:, :n]
     rows = [0, m // 2, m - 1]
     small = buf[rows][:, :n]           # three rows: the smallest calls' policy

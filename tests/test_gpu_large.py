@@ -192,6 +192,39 @@ def test_quantized_rows_beyond_one_launch_are_split(oracle):
     torch.cuda.empty_cache()
 
 
+def test_large_rows_beyond_one_launch_are_split(oracle):
+    """bf16 n = 2^17 in place with 2^16 + 16 rows (16 GiB): two launches of workgroups
+    that share rows, the second with its arrive words and deferred parts behind the
+    first one's in the workspace.  The input is an 8-row seeded block repeated: every
+    row has its block row's bits, and the oracle checks the block."""
+    import torch
+    n, per_launch = 1 << 17, 1 << 16
+    m = per_launch + 16
+    block = W.random_rows(8, n, "bf16", seed=1717)
+    s = W.default_scale(n)
+    say(f"split: bf16 n={n} m={m} in place ({m * n * 2 / 2**30:.1f} GiB)")
+    b = to_device(block, "bf16")
+    ref = H.transform(b)
+    c = compare_with_oracle(oracle, to_host(ref), block, "bf16", s, n)
+    assert c.ok, str(c)
+    x = b.repeat(m // 8 + 1, 1)        # eight rows past m
+    need = H.hadamard_transform_workspace_size(m, n)
+    ws = torch.empty(need + 4096, dtype=torch.uint8, device="cuda")
+    ws[need - 4096:] = 0x5C
+    H.hadamard_transform_ws(x.data_ptr(), n, x.data_ptr(), n, m, n, H.BF16, s, ws.data_ptr(), need,
+                            torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = x.view(torch.int16).view(-1, 8, n)
+    want = ref.view(torch.int16)
+    for r in range(0, m // 8, 1024):
+        assert bool((got[r : min(r + 1024, m // 8)] == want).all()), f"rows from {8 * r} differ"
+    assert torch.equal(got[m // 8], b.view(torch.int16)), "wrote past row m"
+    # parts leave the end of the workspace alone, two passes fill it
+    assert bool((ws[need - 4096:] == 0x5C).all()), "not two launches of shared rows"
+    del x, ws, got
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("L", [17, 20])
 def test_workspace_alignment_picks_store_path_not_result(L):
     """The column pass stores to the workspace with the SC1 cache bit only when

@@ -181,10 +181,11 @@ def test_host_threads_match_serial():
                 assert torch.equal(a, b), f"job {i} differs from the serial result"
 
 
-def test_graph_replays_two_pass_size():
-    """n = 2^17 runs two kernels through the caller's workspace; captured and
+def test_graph_replays_two_pass_size(monkeypatch):
+    """n = 2^17 in two passes, two kernels through the caller's workspace; captured and
     replayed, each replay equals the eager call on the same input."""
     import torch
+    monkeypatch.setenv("HADACORE_VARIANT", "passes")
     m, n = 24, 1 << 17
     gen = torch.Generator(device="cuda").manual_seed(17)
     x = torch.empty(m, n, dtype=torch.bfloat16, device="cuda")

@@ -1,9 +1,11 @@
-"""GPU parity of hadamard_transform_ws against the oracle: n = 2^17 .. 2^20 run
-in two passes through the fp32 workspace, n = 2^16 (the largest one-pass size)
-is reached through the same entry.
+"""GPU parity of hadamard_transform_ws against the oracle: n = 2^17 .. 2^20, and n
+= 2^16 (the largest size without a workspace) through the same entry.  Which way a
+call takes depends on n, m and the mode: with the few rows here 2^17 out of place
+runs by workgroups that share a row, the others in two passes through the fp32
+workspace; tests/test_gpu_parts.py compares the two ways.
 
-Same criterion as the other sizes (tests/metrics.py): the workspace keeps
-every intermediate in fp32, so the result is rounded once.
+Same criterion as the other sizes (tests/metrics.py): every intermediate is fp32,
+so the result is rounded once.
 """
 from __future__ import annotations
 
@@ -226,10 +228,10 @@ def test_large_rows_beyond_one_launch_are_split(oracle):
 
 
 @pytest.mark.parametrize("L", [17, 20])
-def test_workspace_alignment_picks_store_path_not_result(L):
-    """The column pass stores to the workspace with the SC1 cache bit only when
-    the workspace is 128-byte aligned; a 16-byte aligned workspace takes plain
-    stores.  Same output bits, and nothing written past the workspace."""
+def test_workspace_alignment_does_not_change_the_result(monkeypatch, L):
+    """The two passes with a workspace on a 128-byte line and with one that is 16-byte
+    aligned only: same output bits, and nothing written past the workspace."""
+    monkeypatch.setenv("HADACORE_VARIANT", "passes")
     import torch
     n = 1 << L
     m = 3

@@ -1,8 +1,10 @@
 """hadamard_transform_ws_noalloc against hadamard_transform_ws, through the C ABI.
 
-The allocation-free entry point runs the same two-pass kernels as
-hadamard_transform_ws with the workspace taken from the library's fixed device
-array, so its output must equal the workspace call's bit for bit.  Two calls in
+The allocation-free entry point runs the same kernels as hadamard_transform_ws with
+the workspace taken from the library's fixed device array, so its output must equal
+the workspace call's bit for bit: in place 64 rows of 2^17 by workgroups that share
+a row (arrive words in the array), 5 rows of 2^18 in two passes (fp32 intermediates
+in it); out of place the same sizes without and with the array.  Two calls in
 a row, the second on a smaller problem, check that the array's leftover
 contents from the first call do not leak into the second.  A problem whose
 workspace would exceed the array is rejected before anything is enqueued.

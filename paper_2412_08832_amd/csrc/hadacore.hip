@@ -1413,13 +1413,15 @@ __global__ __launch_bounds__(256) void fwht_column_kernel(const uint16_t *in, in
 // per element instead of the two passes' 12.  The operations and their order
 // are the two passes', so the results are the same bits.
 //
-// What bounds it: VALU issue (A/2 * 9 - 1 operations per 2 outputs for the sum of
-// A blocks beside the 16 of the stages: about 21 us for 2^25 elements at A = 4,
-// 30 at 8, 47 at 16) and the L2 reads of A times the input.  Two workgroups per
-// CU overlap one's reads with the other's stages.  Measured against the two
-// passes (bf16, out of place, us): 251 rows of 2^17 72 -> 31, 128 rows of 2^18
-// 73 -> 40, 64 rows of 2^19 75 -> 59.  Summing the blocks on the matrix cores
-// instead was as fast with another order of the sums.
+// What bounds it: VALU issue and the L2 reads of A times the input.  bf16 takes
+// A/2 * 10 - 2 VALU instructions per 2 outputs for the sum of A blocks (4 to widen,
+// 2 products and 2 fmas per pair of blocks, 2 fmas per node of the tree above) and
+// about 32 for the stages and the rounding, 50, 70 and 111 at A = 4, 8, 16: 21, 30 and
+// 47 us for 2^25 elements (fp16, which widens inside the fma, 46, 62 and 95).  Two
+// workgroups per CU overlap one's reads with the other's stages.  Measured against
+// the two passes (bf16, out of place, us): 251 rows of 2^17 72 -> 32, 128 rows of 2^18
+// 70 -> 38, 64 rows of 2^19 71 -> 62.  Summing the blocks on the matrix cores instead
+// was as fast with another order of the sums.
 //
 // TOUCH: while a row is in its stages, its workgroups fetch the lines of their
 // next row into the L2, one 4-byte load per line, a share each (us, without /
@@ -1487,7 +1489,10 @@ __global__ __launch_bounds__(512, 4) void fwht_parts_kernel(
     int64_t m, int groups, uint16_t *defer, uint32_t *arrive, int spin_limit) {
   constexpr int L = kPartL, NW = 8, C = 8;
   constexpr int kPart = 1 << L;
-  constexpr int D = 4;  // loads in flight per lane; 8 spill, and were 0-30% slower
+  // Loads in flight per lane.  With 4, the in-place kernels and A = 16 spill 3 to 7 of
+  // their 128 VGPRs, a few reloads a row, and A = 4 and 8 out of place none; with 8 up
+  // to 44 spill, and they were 0-30% slower.
+  constexpr int D = 4;
   static_assert(A <= 32 - kArriveBits && A >= 2, "one bit of the arrive word per part");
   __shared__ float4 lds[kPart / 4 / 2];
   __shared__ uint32_t seen;  // INPLACE: what thread 0 tells the others of the arrive word

@@ -145,8 +145,8 @@ int64_t hadamard_transform_workspace_size(int64_t m, int64_t n);
  *  - In one pass (most of 2^17 and 2^18, some of 2^19): several workgroups share
  *    a row, each reading all of it and computing a part of the outputs.  In
  *    place they wait for each other's reads through words in the workspace, with
- *    a bounded wait: a part that cannot be stored in time goes through the
- *    workspace.
+ *    a wait that is bounded for the whole launch: a part that cannot be stored in
+ *    time goes through the workspace.
  *  - In two passes (2^20, and the rest): pass 1 applies `scale` and the stages on
  *    index bits 15..log2(n)-1 (between the 2^15-element blocks of a row) into
  *    fp32 values in the workspace, pass 2 the stages on bits 0..14 within each
@@ -172,7 +172,7 @@ hadacore_status hadamard_transform_ws(const void *in, int64_t in_row_stride, voi
  * hadamard_transform_ws_noalloc -- hadamard_transform_ws for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): the same kernels and results, with
- * the fp32 workspace taken from a fixed array inside the library instead of
+ * the workspace taken from a fixed array inside the library instead of
  * an argument.  The call itself allocates nothing (no hipMalloc, hipFree or
  * allocating library routine).
  *   The array is HADACORE_NOALLOC_SCRATCH_BYTES (32 MiB) of device memory per
@@ -184,9 +184,10 @@ hadacore_status hadamard_transform_ws(const void *in, int64_t in_row_stride, voi
  *   Every call on one GPU uses that GPU's one array: calls that can overlap
  *   in time on the same GPU (different streams, host threads) race and give
  *   undefined results; calls in one stream's order are safe.  Nothing in the
- *   array needs to start at zero (every call writes what it reads).  The first call on a device looks up that device's address of the
- *   array (HADACORE_ERROR_LAUNCH if the runtime cannot give it); run that call
- *   outside graph capture.
+ *   array needs to start at zero (every call writes what it reads).  The first
+ *   call on a device looks up that device's address of the array
+ *   (HADACORE_ERROR_LAUNCH if the runtime cannot give it); run that call outside
+ *   graph capture.
  * Other arguments, strides, streams and errors as for hadamard_transform_ws.
  */
 #define HADACORE_NOALLOC_SCRATCH_BYTES (32LL << 20)

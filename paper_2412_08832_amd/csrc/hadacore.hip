@@ -123,17 +123,18 @@ __device__ __forceinline__ void gstore_at(void *base, uint32_t off, u4 v) {
 // Output stores from a wave-uniform base.  With SC1, a nontemporal store also
 // sets the SC1 cache-policy bit, which plain C++ cannot ask for, so it goes
 // out as a raw buffer store (a buffer resource over the 4 GiB from the base,
-// so no range check applies) with the policy NT | SC1.  Measured on MI355X
-// against plain nontemporal stores (interleaved, same box, bit-identical
-// outputs): +1.5% to +3.3% for the wave kernel (n <= 512) and the n <= 8
+// so no range check applies) with the policy NT | SC1.  Measured on MI355X with
+// 2^28 elements against plain nontemporal stores (interleaved, same box,
+// bit-identical outputs): +1.5% to +3.3% for the wave kernel (n <= 512) and the n <= 8
 // kernels, +1% to +2.2% in place at n = 2048-8192, 0 to +2.7% for the
 // quantized outputs, +1.8% for the device copy; but -0.2% to -4% for 16-bit
 // rows of 16384 elements and more, which keep plain nontemporal stores.  A
 // store instruction that leaves part of a 128-byte line unwritten is costly
 // with SC1 (-9% to -18% for unaligned strided rows), so the dispatcher asks
-// for it only where every store writes whole lines (whole_lines).  The cache
-// bits of the loads made no difference.  `base` must be the same in every
-// lane of the wave: it is read from the first active lane.
+// for it only where every store writes whole lines (whole_lines).  At that size
+// the cache bits of the loads made no difference; smaller calls choose theirs, and in
+// place SC1 as well, by size (CallPolicy).  `base` must be the same in every lane of
+// the wave: it is read from the first active lane.
 constexpr int kRsrcWord3 = 0x00020000;  // raw buffer resource word 3 on gfx9: 32-bit data format
 constexpr int kPolicyNtSc1 = 2 | 16;    // buffer cache-policy operand: NT (bit 1) | SC1 (bit 4)
 
@@ -1106,8 +1107,9 @@ __device__ __forceinline__ bool loop_row(u4 (&raw)[C], int64_t row, const uint16
   const bool more = next < m;
   // The quantized epilogues load without a branch (with the loads under
   // `if (more)` the register allocator spills beside the row): a workgroup
-  // past its last row reads row m - 1, the same row for every such
-  // workgroup, so those reads come from cache.
+  // past its last row reads row m - 1, the same row for every such workgroup.
+  // Ordinary loads serve those reads from the caches; streaming loads go past
+  // them, which takes 3 us at 256 rows of n = 65536.
   if (EPI == kStore16 && more) {
     const uint16_t *src = in + next * in_stride;
     const uint32_t ld_off = (uint32_t)(lane_field_load<kMfma, L>(lane) * 16);
@@ -1781,7 +1783,7 @@ __global__ __launch_bounds__(256) void fwht_dense_kernel(const uint16_t *in, uin
 }
 
 // 16-byte streaming copy, one access per thread, the bandwidth reference for
-// the transform (same load and store cache policies as the transform's).
+// the transform (the cache policies of the transform's largest calls).
 template <bool SC1>
 __global__ __launch_bounds__(256) void stream_copy_kernel(const uint16_t *src, uint16_t *dst,
                                                           int64_t count) {
@@ -2380,10 +2382,10 @@ int device_cus() {
 // inside a wave tile (at most 32 rows) below 2^32 bytes.
 constexpr int64_t kMaxStride = int64_t(1) << 26;
 
-// Largest log2 n of one pass (a row of n = 65536 fills the registers of a
-// 512-thread workgroup in fp32) and of hadamard_transform_ws (two passes
-// through the workspace above that).
-constexpr int kMaxOnePassL = 16;
+// Largest log2 n without a workspace (a row of n = 65536 fills the registers of a
+// 512-thread workgroup in fp32) and of hadamard_transform_ws (above that, shared
+// rows or two passes).
+constexpr int kMaxPlainL = 16;
 constexpr int kMaxLargeL = 20;
 
 int log2_exact(int64_t n) {
@@ -2402,7 +2404,7 @@ void row_span(const void *p, int64_t stride, int64_t m, int64_t n, uintptr_t *lo
 // Synchronous argument validation shared by the entry points (no HIP calls).
 hadacore_status validate(const void *in, int64_t in_row_stride, const void *out,
                          int64_t out_row_stride, int64_t m, int64_t n, hadacore_dtype dtype,
-                         float scale, int *L_out, int max_L = kMaxOnePassL) {
+                         float scale, int *L_out, int max_L = kMaxPlainL) {
   if (m < 0) return HADACORE_ERROR_INVALID_VALUE;
   const int L = log2_exact(n);
   if (L < 0 || L > max_L) return HADACORE_ERROR_INVALID_SIZE;
@@ -2433,10 +2435,9 @@ hadacore_status validate(const void *in, int64_t in_row_stride, const void *out,
 // long, alive until the process ends.  Host code never uses the symbol's name
 // as an address: on its first call on a device the entry point asks the
 // runtime for that device's address of the array (hipGetSymbolAddress, with
-// the device current) and keeps it here.  Every call
-// writes (or clears, in a launch of its own) what it reads of the workspace, so
-// nothing needs clearing between calls; calls that overlap on one GPU share the
-// array and race.
+// the device current) and keeps it here.  Every call writes (or clears, in a launch
+// of its own) what it reads of the workspace, so nothing needs clearing between
+// calls; calls that overlap on one GPU share the array and race.
 constexpr int64_t kScratchBytes = HADACORE_NOALLOC_SCRATCH_BYTES;
 __device__ __align__(256) float scratch[kScratchBytes / sizeof(float)];
 
@@ -2491,7 +2492,7 @@ extern "C" hadacore_status hadamard_transform_strided(const void *in, int64_t in
 
 extern "C" int64_t hadamard_transform_workspace_size(int64_t m, int64_t n) {
   const int L = log2_exact(n);
-  if (m <= 0 || L <= kMaxOnePassL || L > kMaxLargeL || m >= (int64_t(1) << 31)) return 0;
+  if (m <= 0 || L <= kMaxPlainL || L > kMaxLargeL || m >= (int64_t(1) << 31)) return 0;
   if (m > (int64_t(1) << 40) / n) return 0;  // the call itself reports TOO_LARGE
   return 4 * m * n;
 }
@@ -2502,7 +2503,7 @@ namespace {
 // hadamard_transform_ws after its workspace has been chosen: `workspace` of
 // `workspace_bytes`, or with `fixed` the scratch array (whose size is the
 // limit, reported as HADACORE_ERROR_SCRATCH).
-hadacore_status transform_two_pass(const void *in, int64_t in_row_stride, void *out,
+hadacore_status transform_large(const void *in, int64_t in_row_stride, void *out,
                                    int64_t out_row_stride, int64_t m, int64_t n,
                                    hadacore_dtype dtype, float scale, void *workspace,
                                    int64_t workspace_bytes, bool fixed, void *stream) {
@@ -2510,7 +2511,7 @@ hadacore_status transform_two_pass(const void *in, int64_t in_row_stride, void *
   const hadacore_status st =
       validate(in, in_row_stride, out, out_row_stride, m, n, dtype, scale, &L, kMaxLargeL);
   if (st != HADACORE_SUCCESS || m == 0) return st;
-  if (L <= kMaxOnePassL) {
+  if (L <= kMaxPlainL) {
     return hadamard_transform_strided(in, in_row_stride, out, out_row_stride, m, n, dtype, scale,
                                       stream);
   }
@@ -2561,7 +2562,7 @@ extern "C" hadacore_status hadamard_transform_ws(const void *in, int64_t in_row_
                                                  hadacore_dtype dtype, float scale,
                                                  void *workspace, int64_t workspace_bytes,
                                                  void *stream) {
-  return transform_two_pass(in, in_row_stride, out, out_row_stride, m, n, dtype, scale, workspace,
+  return transform_large(in, in_row_stride, out, out_row_stride, m, n, dtype, scale, workspace,
                             workspace_bytes, false, stream);
 }
 
@@ -2570,7 +2571,7 @@ extern "C" hadacore_status hadamard_transform_ws_noalloc(const void *in, int64_t
                                                          int64_t m, int64_t n,
                                                          hadacore_dtype dtype, float scale,
                                                          void *stream) {
-  return transform_two_pass(in, in_row_stride, out, out_row_stride, m, n, dtype, scale, nullptr, 0,
+  return transform_large(in, in_row_stride, out, out_row_stride, m, n, dtype, scale, nullptr, 0,
                             true, stream);
 }
 
@@ -2589,7 +2590,7 @@ hadacore_status transform_quantized(const void *in, int64_t in_row_stride, void 
                                     int64_t n, hadacore_dtype dtype, float scale, void *stream) {
   if (m < 0) return HADACORE_ERROR_INVALID_VALUE;
   const int L = log2_exact(n);
-  if (L < 0 || L > kMaxOnePassL) return HADACORE_ERROR_INVALID_SIZE;
+  if (L < 0 || L > kMaxPlainL) return HADACORE_ERROR_INVALID_SIZE;
   if (dtype != HADACORE_FP16 && dtype != HADACORE_BF16) return HADACORE_ERROR_INVALID_DTYPE;
   if (!isfinite(scale)) return HADACORE_ERROR_INVALID_VALUE;
   // input rows start on 2*min(n, 8)-byte boundaries, code rows on min(n, 16)

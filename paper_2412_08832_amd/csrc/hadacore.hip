@@ -1885,6 +1885,15 @@ CallPolicy in_place_policy(int L, int64_t e, bool whole, int64_t gap_bytes) {
   return {cached, whole && !cached};
 }
 
+// Front end used unless HADACORE_VARIANT forces one: the matrix cores from
+// n = 4096 for 16-bit output, everywhere from n = 128 for quantized output.
+// Below n = 128 there is only the VALU front (the radix-32 step needs 16 vectors
+// of 32 elements per wave with four lanes per vector row group).
+template <int L, int EPI>
+constexpr int default_front() {
+  return L >= 7 && (EPI != kStore16 || L >= 12) ? kMfma : kValu;
+}
+
 // C: chunks per lane; T: tiles per wave (wave kernel) ; WPB: waves per workgroup
 // (wave kernel); HALVES: LDS exchange passes (block kernel); FRONT: kValu / kMfma.
 template <int DT, int L, int C, int T, int WPB, int HALVES, int FRONT, int EPI = kStore16>
@@ -1947,7 +1956,10 @@ hipError_t launch_cfg(const uint16_t *in, int64_t in_stride, uint16_t *out, int6
     // 16-bit rows of 2^14 and more store without SC1 (see gstore_u)
     constexpr std::bool_constant<(EPI != kStore16 || L <= 13) && !(L == 16 && FRONT == kMfma)>
         may_sc1{};
-    constexpr std::bool_constant<!(L == 16 && EPI == kStore16)> may_cache{};
+    // a forced front end always streams: its ordinary-load kernels were a fifth of the
+    // library (5.6 -> 4.5 MB), for testing only
+    constexpr std::bool_constant<!(L == 16 && EPI == kStore16) && FRONT == default_front<L, EPI>()>
+        may_cache{};
     if (sc1) {
       if (cached)
         launch_as(may_sc1, may_cache);
@@ -2016,15 +2028,6 @@ constexpr Cfg config() {
     if constexpr (L <= 15) return {8, 1, 1, 2};
     return {16, 1, 1, 2};
   }
-}
-
-// Front end used unless HADACORE_VARIANT forces one: the matrix cores from
-// n = 4096 for 16-bit output, everywhere from n = 128 for quantized output.
-// Below n = 128 there is only the VALU front (the radix-32 step needs 16 vectors
-// of 32 elements per wave with four lanes per vector row group).
-template <int L, int EPI>
-constexpr int default_front() {
-  return L >= 7 && (EPI != kStore16 || L >= 12) ? kMfma : kValu;
 }
 
 template <int DT, int L, int EPI, int FRONT>

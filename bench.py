@@ -20,7 +20,8 @@ named workloads and over sampled rows of the sweep points, compares it with one
 fresh-copy call of the transform per point, and times the oracle on the
 headline workload on the host cores.
 
-Prints ONE JSON line; per-point results are in config.points.
+Prints ONE JSON line of a few KB; each point's main results are in config.points,
+and ``--points FILE`` writes the full records, one JSON line each, to FILE.
 ``--workload NAME`` measures one workload only (used for profiling).
 ``--sweep FILE`` additionally writes one JSON line per extended point
 (n = 2^0..2^20, FP8 and INT8 outputs) to FILE.
@@ -67,6 +68,8 @@ def parse_args(argv=None):
                    help="measure one workload only: a named workload or "
                         "sweep:<dtype>:<log2 n>:<in|out>")
     p.add_argument("--sweep", metavar="FILE", help="also time the extended points, one JSON line each")
+    p.add_argument("--points", metavar="FILE",
+                   help="also write every point's full record, one JSON line each")
     p.add_argument("--fp8", action="store_true",
                    help="with --workload: the fused transform + e4m3 quantization")
     p.add_argument("--int8", action="store_true",
@@ -465,6 +468,20 @@ def run_single(args, d: Device) -> dict:
     return line
 
 
+def point_summary(rec: dict) -> dict:
+    """The part of a point's record that goes into the printed line, rounded: the line of
+    40 points stays short enough to be kept whole by whoever reads the last few KB of
+    the output."""
+    par = rec.get("parity")
+    return {
+        "workload": rec["workload"], "gbs": round(rec["gbs"], 1),
+        "frac_hbm_peak": round(rec["frac_hbm_peak"], 4),
+        "frac_of_copy": round(rec["frac_of_copy"], 4),
+        "rel_l2": float(f"{par['rel_l2']:.3e}") if par else None,
+        "parity_ok": par["ok"] if par else None,
+    }
+
+
 def run_all(args, d: Device) -> dict:
     from paper_2412_08832_amd import workloads as W
     points = []
@@ -508,7 +525,9 @@ def run_all(args, d: Device) -> dict:
     w = W.WORKLOADS[HEADLINE]
     line = headline_line(args, w, head_rec)
     fr = [p["frac_hbm_peak"] for p in points]
-    line["config"]["points"] = points
+    line["config"]["points"] = [point_summary(p) for p in points]
+    if args.points:
+        Path(args.points).write_text("".join(json.dumps(p) + "\n" for p in points))
     line["config"]["summary"] = {
         "points": len(points),
         "parity_checked": sum(1 for p in points if "parity" in p),

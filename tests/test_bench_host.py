@@ -3,6 +3,7 @@ the traffic figure read from the committed rocprofv3 summaries, and the
 paper-context object of the JSON line."""
 from __future__ import annotations
 
+import json
 import re
 import subprocess
 import sys
@@ -158,6 +159,34 @@ def test_counter_summaries_cover_both_front_ends():
 def test_every_summary_is_checked():
     assert len(PROFILES) + len(COUNTER_SUMMARIES) == len(list(bench.PROFILES.glob("*.txt")))
     assert PROFILES, "no kernel-trace summaries"
+
+
+def test_the_line_of_the_default_run_is_short():
+    """All 40 points in the printed line, with long values: at most 8,000 characters
+    with the rest of the line (a reader that keeps the last 13,000 characters lost the
+    start of a 38,000-character line), and no figure is lost to rounding."""
+    rec = {"workload": "sweep_bf16_n32768_outofplace", "dtype": "bf16", "m": 8192, "n": 32768,
+           "inplace": False, "output": "bf16", "rotating_buffers": 2,
+           "ms_per_call": 0.17698989868164064, "ms_per_call_first_region": 0.17700510025024416,
+           "gbs": 6066.6842119130515, "frac_hbm_peak": 0.7583355264891314,
+           "copy_gbs": 6633.933446438149, "frac_of_copy": 0.9144927758011107,
+           "memcpy_gbs": 5345.14224299935, "frac_of_memcpy": 1.1349902277827537,
+           "alg_bytes_per_call": 1 << 30, "meets_target": False,
+           "parity": {"rel_l2": 0.00020772695773880242, "ok": False}}
+    args = bench.parse_args([])
+    n_points = len(bench.NAMED) + 4 * len(list(bench.SWEEP_LOG2))
+    assert n_points == 40
+    line = bench.headline_line(args, W.WORKLOADS[bench.HEADLINE], rec)
+    line["config"]["points"] = [bench.point_summary(rec)] * n_points
+    line["cpu_baseline"] = bench.cpu_baseline(W.WORKLOADS["fp16_1024x256"], 0.05)
+    assert len(json.dumps(line)) <= 8_000 - 400       # config.summary, bench_wall_s
+    p = bench.point_summary(rec)
+    assert p["workload"] == rec["workload"] and p["parity_ok"] is False
+    for key in ("gbs", "frac_hbm_peak", "frac_of_copy"):
+        assert p[key] == pytest.approx(rec[key], rel=1e-4)
+    assert p["rel_l2"] == pytest.approx(rec["parity"]["rel_l2"], rel=1e-3)
+    del rec["parity"]
+    assert bench.point_summary(rec)["rel_l2"] is None
 
 
 def test_paper_context_is_context_only():

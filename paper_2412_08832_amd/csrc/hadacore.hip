@@ -2202,19 +2202,20 @@ struct LargeMode {
 //    51.2 / 66.1 / 85.7 / 61.2, and 44.1 / 59.0 / 77.7 / 62.8 without fetching; 65 rows
 //    70 / 90 / 121 / 81 against 73 / 92 / 117 / 78, and 66 / 86 / 116 / 95; 96 rows 94 /
 //    134 / 164 / 105 against 98 / 139 / 177 / 107, and 110 / 138 / 159 / 122).  Below,
-//    parts gain on warm buffers at some sizes and lose more cold (16 rows 20.2 / 26.4 /
-//    34.0 / 29.1 against 24.7 / 26.9 / 35.1 / 25.4; 40 rows 40.7 / 53.2 / 69.4 / 61.5
-//    against 43.5 / 55.6 / 71.6 / 53.4), or lose everywhere (8 rows 16.4 / 23.6 / 25.6 /
-//    27.0 against 18.6 / 18.4 / 22.8 / 18.7; 17 rows 28.2 / 34.8 / 42.8 / 42.4 against
-//    26.3 / 31.5 / 39.0 / 31.3).
+//    parts gain on warm buffers at some sizes and lose more elsewhere (8 rows 16.4 /
+//    23.6 / 25.6 / 27.0 against 18.6 / 18.4 / 22.8 / 18.7; 16 rows 20.2 / 26.4 / 34.0 /
+//    29.1 against 24.7 / 26.9 / 35.1 / 25.4; 40 rows 40.7 / 53.2 / 69.4 / 61.5 against
+//    43.5 / 55.6 / 71.6 / 53.4), or lose everywhere (17 rows 28.2 / 34.8 / 42.8 / 42.4
+//    against 26.3 / 31.5 / 39.0 / 31.3).
 //  - In place the clearing launch and the waits cost 4 us and more.  2^17 from 12 rows
 //    (12.3 / 15.9 / 18.6 / 19.8 against 14.2 / 16.4 / 19.5 / 16.2; 8 rows 12.0 / 15.2 / 17.3
-//    / 19.7 against 12.8 / 14.6 / 17.0 / 15.6), never fetching ahead (768 rows 110 / 183 /
-//    260 / 121 with, 111 / 179 / 264 / 116 without).  2^18 from 16 rows (15.4 / 21.5 /
-//    23.2 / 25.0 against 19.9 / 22.3 / 26.1 / 21.6; 9 rows 14.4 / 19.2 / 21.9 / 23.5
-//    against 17.8 / 19.3 / 22.2 / 17.4), fetching ahead from 192.  2^19 never (32 rows
-//    37.4 / 46.2 / 61.3 / 52.3 against 35.6 / 43.7 / 56.8 / 44.0, 128 rows 134 / 186 / 224
-//    / 145 against 128 / 181 / 231 / 141).
+//    / 19.7 against 12.8 / 14.6 / 17.0 / 15.6), fetching ahead from 2^27 elements, 1024
+//    rows (142 / 242 / 341 / 154 with, 148 / 243 / 348 / 154 without; 384 rows 61 / 93 /
+//    131 / 72 and 60 / 98 / 133 / 68, 768 rows 109 / 184 / 261 / 122 and 113 / 182 / 267 /
+//    118).  2^18 from 16 rows (15.4 / 21.5 / 23.2 / 25.0 against 19.9 / 22.3 / 26.1 /
+//    21.6; 9 rows 14.4 / 19.2 / 21.9 / 23.5 against 17.8 / 19.3 / 22.2 / 17.4), fetching
+//    ahead from 192.  2^19 never (32 rows 37.4 / 46.2 / 61.3 / 52.3 against 35.6 / 43.7 /
+//    56.8 / 44.0, 128 rows 134 / 186 / 224 / 145 against 128 / 181 / 231 / 141).
 bool parts_pay(int L, int64_t m, bool inplace) {
   if (inplace) return L == 17 ? m >= 12 : L == 18 && m >= 16;
   return L == 17 || (L == 18 ? m >= 8 : 2 * m >= 3 * parts_groups(16));
@@ -2223,7 +2224,7 @@ bool parts_pay(int L, int64_t m, bool inplace) {
 bool parts_touch(int L, int64_t m, bool inplace) {
   if (L == 19) return true;
   if (L == 18 && !inplace && 4 * m <= parts_groups(8)) return true;
-  return !(L == 17 && inplace) && m << L >= 3 << 24;
+  return m << L >= (L == 17 && inplace ? 1 << 27 : 3 << 24);
 }
 
 template <int DT, int LN>
@@ -2238,12 +2239,10 @@ hipError_t launch_large_size(const uint16_t *in, int64_t in_stride, uint16_t *ou
         return launch_parts<DT, A, decltype(with_inplace)::value, decltype(with_touch)::value>(
             in, in_stride, out, out_stride, m, scale, ws, mode.spin_limit, stream);
       };
-      // parts_touch never holds for LN = 17 in place and always does for LN = 19
-      constexpr std::bool_constant<LN == 19> always{};
+      constexpr std::bool_constant<LN == 19> always{};  // parts_touch always holds there
       const bool touch = parts_touch(LN, m, inplace);
       if (inplace)
-        return touch ? parts(std::true_type{}, std::bool_constant<LN != 17>{})
-                     : parts(std::true_type{}, always);
+        return touch ? parts(std::true_type{}, std::true_type{}) : parts(std::true_type{}, always);
       return touch ? parts(std::false_type{}, std::true_type{}) : parts(std::false_type{}, always);
     }
   }

@@ -83,7 +83,8 @@ def test_parts_match_oracle_and_two_passes(oracle, monkeypatch, L, m, dtype):
     (17, 1, False, True), (18, 7, False, False), (18, 8, False, True), (18, 16, False, True),
     (18, 17, False, True), (18, 192, False, True), (19, 16, False, False), (19, 17, False, False),
     (19, 40, False, False), (19, 47, False, False), (19, 48, False, True), (19, 65, False, True),
-    (17, 11, True, False), (17, 12, True, True), (17, 384, True, True), (18, 15, True, False),
+    (17, 11, True, False), (17, 12, True, True), (17, 384, True, True), (17, 1023, True, True),
+    (17, 1024, True, True), (18, 15, True, False),
     (18, 16, True, True), (18, 192, True, True), (19, 96, True, False)])
 def test_path_by_size(monkeypatch, L, m, inplace, parts):
     """Both sides of each line of the dispatch: which way a call takes, seen from the

@@ -1838,9 +1838,10 @@ struct CallPolicy {
 // Out of place.  Gains of ordinary loads in percent, in the four states rot / prod /
 // pipe / cold; cold is 0 to -4 with a cache full of unmodified data, and a reader of
 // the input after the call, timed along, gains 7 to 13.
-//  - 16 bits, up to 3 * 2^23 elements: +2 to +20 / -2 to +1 / -2 to 0 / -5 to -19.  Above,
-//    where input, output and what reads it no longer fit the cache together, pipe
-//    loses 3 to 6 at 2^24.75 and 8 at 2^25, against +10 to +16 in rot: they stream.
+//  - 16 bits, up to 7 * 2^22 elements (56 MiB): +2 to +20 / -2 to +1 / -2 to 0 / -5 to
+//    -19, at 2^24.75 pipe -3 to -6.  Above, input, output and what reads it no longer
+//    fit the cache together: at 2^25 pipe loses 7 to 8 and cold 12 to 18, against +9 to
+//    +16 in rot, so these calls stream.
 //    The lower ends differ: 2^23 gains 9-14 in rot up to n = 1024, and above it loses
 //    1-9 in rot and 4-5 in prod; n = 32768 loses 4 in rot up to 2^24.
 //  - Quantized, up to 2^25: +1 to +18 / -5 to +1 / -3 to 0 / -9 to -23, from 2^23 (n <=
@@ -1850,7 +1851,7 @@ struct CallPolicy {
 //    ending workgroups all read the last row once more.
 bool cached_out_of_place(int epi, int L, int64_t e) {
   if (epi == kStore16)
-    return e <= 3 << 23 && (L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24);
+    return e <= 7 << 22 && (L <= 10 ? e >= 1 << 23 : L <= 14 ? e > 1 << 23 : L == 15 && e > 1 << 24);
   if (e > 1 << 25) return false;
   if (L == 16) return e >= 1 << 22;
   return L <= 7 ? e >= 1 << 23 : L <= 10 ? e > 1 << 23 : e > 1 << 24;

@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # some rule (16 bits out of place, quantized, in place with whole lines or rows that
 # share lines) changes, one row fewer and one more
 SIZES = [(1 << L, total) for L in range(4, 17)
-         for total in (1 << 23, 1 << 24, 3 << 23, 1 << 25)] + [(65536, 1 << 22)]
+         for total in (1 << 23, 1 << 24, 7 << 22, 1 << 25)] + [(65536, 1 << 22)]
 
 
 @pytest.mark.parametrize("dtype", ["fp16", "bf16"])
